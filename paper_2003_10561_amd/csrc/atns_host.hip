@@ -284,7 +284,7 @@ Stage6Args<T> base6(at_sim* s) {
   a.ring = (T*)(s->ws + s->L.ring);
   a.gv = (T*)(s->ws + s->L.gv);
   a.tot_part = (double*)(s->ws + s->L.tot_part);
-  tile6_of(s->g, &a.bx, &a.by);
+  a.tile = tile6_of(s->g);
   a.delays = s->d_sched ? s->d_sched + (size_t)s->step * s->g.ntiles * 6 : s->d_zero;
   a.step_mod_r = (int)(s->step % s->g.R);
   a.mode = kModeStepH;

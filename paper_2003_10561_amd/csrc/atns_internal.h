@@ -170,8 +170,11 @@ int64_t paper_blocks(const Geom& g);
 template <typename T>
 hipError_t launch_stagep(const StagePArgs<T>& s, int which, hipStream_t stream);
 
-// Sixth-order stage (stage6.hip): gradients and fluxes, then divergence and update; tiles of
-// bx x by columns inside one PE, one workgroup per (tile, z-PE).
+// Sixth-order stage (stage6.hip): gradients and fluxes, then divergence and update; workgroups of
+// bx x by columns inside one PE, marching through zc of its planes.
+struct Tile6 {
+  int bx, by, zc;
+};
 template <typename T>
 struct Stage6Args {
   Geom g;
@@ -186,14 +189,14 @@ struct Stage6Args {
   T* rhs_out;
   const int8_t* delays;
   double* tot_part;
-  int bx, by;
+  Tile6 tile;
   int step_mod_r, publish, store_dq, mode;
   T cs, rk_a, rk_b, dt, c_prev;
   T cs3[3];           // the ghost pass: c_s of each of its nst stages
   int nst;
   double vol;
 };
-void tile6_of(const Geom& g, int* bx, int* by);
+Tile6 tile6_of(const Geom& g);
 int64_t blocks6(const Geom& g);
 // gradflux: the gradient / flux launch; otherwise the divergence / update launch
 template <typename T>

@@ -1,0 +1,77 @@
+"""Work splits at the sizes where they can go wrong, against the CPU FP64 oracle: tiles narrower than
+their neighbours, PEs cut along z, threads with two halo points, grids smaller than one tile.  FP64
+bars as in the parity tests: relative L2 <= 1e-12 per component (a ghost value carries the rounding
+of its terms times at most 31)."""
+import numpy as np
+import pytest
+
+from oracle import Oracle, OracleConfig
+from paper_2003_10561_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2003_10561_amd import atns  # noqa: E402
+
+TOL64 = 1e-12
+
+
+def smooth_levels(n, nlev, seed, form):
+    """Smooth periodic states that drift in time: (rho, m, E) or (rho, m, rho e)."""
+    rng = np.random.default_rng(seed)
+    x, y, z = (2 * np.pi * np.arange(m) / m for m in n)
+    Z, Y, X = np.meshgrid(z, y, x, indexing="ij")
+    ph = rng.uniform(0, 2 * np.pi, (5, 3))
+    out = np.empty((nlev, 5) + X.shape)
+    for lv in range(nlev):
+        s = 0.05 * lv
+        f = [np.sin(X + ph[i, 0] + s) * np.cos(Y + ph[i, 1]) + 0.5 * np.sin(Z + ph[i, 2] - s) for i in range(5)]
+        rho, t = 1 + 0.1 * f[0], 1 + 0.1 * f[4]
+        u = [0.3 * g for g in f[1:4]]
+        out[lv, 0] = rho
+        for i in range(3):
+            out[lv, 1 + i] = rho * u[i]
+        out[lv, 4] = rho * 2.5 * t + (0.5 * rho * sum(v * v for v in u) if form == 0 else 0)
+    return out
+
+
+def check(n, p, order=4, form=0, steps=2, precision="fp64", tol=TOL64, tune=None):
+    nlev = 7
+    q = smooth_levels(n, nlev, sum(n), form)
+    kw = dict(n=n, p=p, dt=2e-3, mu_ref=0.02, max_delay=3, order=order, form=form)
+    g = atns.Sim(atns.Config(precision=precision, **kw))
+    o = Oracle(OracleConfig(**kw))
+    g.init_field(q, nlev)
+    o.init_field(q, nlev)
+    tab = np.random.default_rng(sum(p)).integers(0, 4, (nlev + steps, p[0] * p[1] * p[2], 6)).astype(np.int8)
+    tab[:nlev - 1] = 0
+    g.set_delay_schedule(atns.EXPLICIT, table=tab)
+    o.set_schedule(atns.EXPLICIT, table=tab)
+    if tune:
+        g.set_stage_tuning(*tune)
+
+    def same(a, b, what):
+        err = max(float(np.linalg.norm(a[c] - b[c]) / np.linalg.norm(b[c])) for c in range(5))
+        print(f"case n={n} p={p} order={order} form={form} {precision} {what}: rel-L2 {err:.2e}", flush=True)
+        assert err <= tol, (what, err)
+
+    if precision == "fp64":
+        same(g.rhs().cpu().numpy(), o.rhs(), "rhs")
+    g.rk_step(steps)
+    o.rk_step(steps)
+    same(g.get_field(), o.field(), "fields")
+    gs, os_ = g.stats(), o.stats()
+    for k in ("mass", "energy", "mass_rk", "K", "eps", "enstrophy", "Mt", "umax"):
+        assert abs(gs[k] - os_[k]) <= max(tol, 1e-12) * abs(os_[k]), (k, gs[k], os_[k])
+    g.close()
+
+
+# edges: 6 (the smallest PE: 36 columns, two halo points a thread), 7 (one partial tile in z), 21 and
+# 25 (odd), 33 (tiles of 17 + 16), 65 (of 33 + 32), 40 along z (cut into chunks of 8)
+@pytest.mark.parametrize("n,p", [((6, 6, 6), (1, 1, 1)), ((12, 14, 40), (2, 2, 1)), ((42, 25, 33), (2, 1, 1)),
+                                 ((33, 21, 24), (1, 1, 3)), ((130, 9, 12), (2, 1, 1))])
+def test_order6_tiles(n, p):
+    check(n, p, order=6)
