@@ -100,6 +100,58 @@ Geom make_geom(const at_config* c) {
   return g;
 }
 
+// Cost of one plane of a workgroup's march in microseconds, measured on grids of 32^3 to 270 x 200 x
+// 150: `alone`, with the workgroup the only one of its compute unit (latency), and `busy`, per
+// workgroup with the compute unit full (throughput).  A workgroup of zc planes marches through
+// zc + 4, so a stage of n workgroups on 256 compute units takes about
+// (zc + 4) max(alone, ceil(n / 256) busy), rounded off where the two meet (their fourth powers are
+// added): within 10% of the times measured with 32 x 8 tiles on 32^3 (18.3 us with z chunks of 4, 43
+// with 16), 128^3 and 256^3.  Rows: FP32, FP64; per row stages
+// without AT stencils, with AT on tiles aligned with the PEs, with masked AT.  Tiles that won nowhere
+// are left out; the first of a row is taken unless another saves 5%.
+struct ShapeCost {
+  int tile;
+  double alone, busy;
+};
+constexpr int kShapes = 4;
+constexpr ShapeCost kShapeCost[2][3][kShapes] = {
+    {{{1, 2.05, 1.57}, {0, 1.8, 2.9}, {5, 2.0, 1.14}, {6, 2.2, 1.77}},
+     {{1, 3.0, 2.35}, {0, 2.8, 4.0}, {5, 2.7, 1.35}, {6, 3.2, 3.8}},
+     {{1, 3.2, 3.1}, {5, 3.0, 2.4}, {6, 3.4, 3.3}, {0, 5.0, 7.3}}},
+    {{{1, 2.5, 3.65}, {5, 2.95, 2.09}, {6, 2.6, 3.7}, {3, 3.0, 3.3}},
+     {{5, 3.0, 4.36}, {1, 6.0, 9.7}, {6, 6.0, 8.9}, {3, 5.6, 8.4}},
+     {{5, 3.0, 4.8}, {1, 6.0, 13.0}, {6, 6.0, 13.0}, {3, 5.6, 8.6}}}};
+constexpr int kComputeUnits = 256;
+
+// Small grids are cut into short z chunks so that they reach every compute unit (32^3 in FP64 ran on
+// 4 of them, 300 us a delayed stage; now 40), large ones into long ones (fewer planes twice).
+void default_shape(const Geom& g, int precision, bool forced, bool at, int* tile, int* zchunk) {
+  const int row = precision == AT_FP32 ? 0 : 1;
+  double least = 1e300;
+  for (int i = 0; i < kShapes; ++i) {
+    const int t = kShapeCost[row][at ? 1 : 0][i].tile;
+    if (fused_lds_bytes(t, row == 0 ? 4 : 8, forced) > kLdsBytes) continue;
+    const ShapeCost* c = kShapeCost[row][!at ? 0 : tile_aligned(g, t) ? 1 : 2];
+    while (c->tile != t) ++c;  // each row of a precision lists the same tiles with AT stencils
+    double best = 1e300;
+    int zbest = g.n[2];
+    for (int nc = 1; nc <= g.n[2] / 4; nc += nc < 16 ? 1 : nc / 8) {
+      const int zc = (g.n[2] + nc - 1) / nc;
+      const double rounds = (double)((fused_blocks(g, t, zc) + kComputeUnits - 1) / kComputeUnits);
+      const double cost = (zc + 4) * std::sqrt(std::sqrt(std::pow(c->alone, 4) + std::pow(rounds * c->busy, 4)));
+      if (cost < best) {
+        best = cost;
+        zbest = zc;
+      }
+    }
+    if (best < (i ? 0.95 : 1.0) * least) {
+      least = best;
+      *tile = t;
+      *zchunk = std::max(4, zbest);
+    }
+  }
+}
+
 }  // namespace atns
 
 namespace {
@@ -642,12 +694,8 @@ int at_create(const at_config* cfg, void* ws, size_t ws_bytes, void* stream, at_
   s->L = L;
   s->stream = (hipStream_t)stream;
   s->ws = (uint8_t*)ws;
-  // default launch shape: 32 x 8 columns if it fits the LDS at this precision, else 16 x 8
-  s->tile = fused_lds_bytes(1, cfg->precision == AT_FP32 ? 4 : 8, cfg->forcing != 0) <= kLdsBytes ? 1 : 5;
-  s->zchunk = cfg->n[2] / cfg->p[2] >= 16 ? cfg->n[2] / cfg->p[2] : cfg->n[2];
-  if (s->zchunk > 128) s->zchunk = 128;
-  s->tile_d = s->tile;
-  s->zchunk_d = s->zchunk;
+  default_shape(g, cfg->precision, cfg->forcing != 0, false, &s->tile, &s->zchunk);
+  default_shape(g, cfg->precision, cfg->forcing != 0, true, &s->tile_d, &s->zchunk_d);
   hipError_t e = hipGetDevice(&s->device);
   if (e == hipSuccess) e = hipMalloc(&s->d_zero, (size_t)g.ntiles * 6);
   if (e == hipSuccess) e = hipMemsetAsync(s->d_zero, 0, (size_t)g.ntiles * 6, s->stream);

@@ -80,6 +80,10 @@ int validate(const at_config* c);
 // Grid, PE and ring geometry of a valid configuration.
 Geom make_geom(const at_config* c);
 
+// Launch shape a single run takes by itself for its stages that read no delayed level, or (at) for
+// those that do, by the cost model in atns_host.hip.
+void default_shape(const Geom& g, int precision, bool forced, bool at, int* tile, int* zchunk);
+
 // Removes a run from its batch (called when the run is destroyed).
 void batch_forget(at_batch* b, at_sim* s);
 
