@@ -11,11 +11,16 @@
 // standard fourth-order one-sided and biased stencils on the two points next to a face), then the
 // average.  Viscosity: the power law or Sutherland's law (Sec. 2).
 //
-// Launches: per stage kp_grad (the 12 AT gradients of u, v, w, T into a workspace buffer; at stage 1
+// Launches: per stage kp_grad (the nine AT gradients of u, v, w into a workspace buffer; at stage 1
 // of a step the points of every PE's two layers next to each face also publish their conserved
-// variables into ring slot n mod R) and kp_rhs (every term above at one point per thread, the
-// gradients of the PE-local mixed-derivative lines read back from that buffer, then the Runge-Kutta
-// or Adams-Bashforth update and FP64 block totals); kp_publish publishes a history level alone.
+// variables into ring slot n mod R), kp_mixed (the three sums of mixed derivatives, from the PE-local
+// lines of the gradients in that buffer) and kp_rhs (every other term above, then the Runge-Kutta or
+// Adams-Bashforth update and FP64 block totals; it forms the 12 gradients at its own point again from
+// the neighbours it holds, which cost 48 bytes a point when read); kp_publish publishes a history
+// level alone.  The
+// mixed sums travel in the first three components of the buffer that kp_rhs is about to write.
+#include <algorithm>
+
 #include "atns_internal.h"
 
 namespace atns {
@@ -29,7 +34,8 @@ struct PA {
   const T* q;
   T* q_out;
   T* dq;
-  T* grad;           // [12][N]: du_i/dx_j at 3 i + j, then dT/dx_j at 9 + j
+  T* grad;           // [9][N]: du_i/dx_j at 3 i + j
+  T* mix;            // [3][N]: sums of mixed derivatives (the head of q_out, or of rhs_out)
   T* ring;
   T* rhs_out;
   const int8_t* delays;
@@ -38,6 +44,8 @@ struct PA {
   int n[3], e[3], p[3];
   uint32_t slab[3], rdir[3], rslot;  // ring element: slot rslot + rdir[d] + c slab[d] + j
   int R, step_mod_r, slot, store_dq, mode;
+  int zc, zcm;       // planes of a brick of kp_grad / kp_rhs and of kp_mixed
+  int tw[2], tn[2], tz;  // tile: largest width along x and y, tiles of a PE along them; planes
   T cs, rk_a, rk_b, dt, c_prev;
   T gas_r, inv_cv, cp_over_pr, mu_ref, inv_tref, mu_exp, suth_s;
   int visc;
@@ -144,30 +152,6 @@ __device__ __forceinline__ T viscosity(const PA<T>& a, T temp, T* dmu) {
   return mu;
 }
 
-// Derivative along direction d of gradient component gc at point i (local index l inside its
-// PE of edge e) from the PE's own points: central (1,4) for 2 <= l <= e - 3, else the standard
-// fourth-order one-sided (l = 0, e - 1) and biased (l = 1, e - 2) stencils.
-template <typename T>
-__device__ __forceinline__ T pe_d1(const PA<T>& a, int gc, int d, uint32_t i, int l) {
-  const int e = a.e[d];
-  const uint32_t st = d == 0 ? 1u : (d == 1 ? (uint32_t)a.n[0] : (uint32_t)a.n[0] * a.n[1]);
-  const T* g = a.grad + (uint32_t)gc * a.N + i;
-  auto at = [&](int o) { return g[(int64_t)o * (int64_t)st]; };
-  T s;
-  if (l >= 2 && l <= e - 3) {
-    s = (at(-2) - T(8) * at(-1)) + (T(8) * at(1) - at(2));
-  } else if (l == 0) {
-    s = ((T(-25) * at(0) + T(48) * at(1)) - T(36) * at(2)) + (T(16) * at(3) - T(3) * at(4));
-  } else if (l == 1) {
-    s = ((T(-3) * at(-1) - T(10) * at(0)) + T(18) * at(1)) + (T(-6) * at(2) + at(3));
-  } else if (l == e - 2) {
-    s = ((T(3) * at(1) + T(10) * at(0)) - T(18) * at(-1)) + (T(6) * at(-2) - at(-3));
-  } else {
-    s = ((T(25) * at(0) - T(48) * at(-1)) + T(36) * at(-2)) + (T(-16) * at(-3) + T(3) * at(-4));
-  }
-  return s * a.i12h[d];
-}
-
 __device__ __forceinline__ double wsum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -272,11 +256,10 @@ __global__ __launch_bounds__(256) void kp_publish(PA<T> a) {
   for (int c = 0; c < 5; ++c) dst[(uint32_t)c * a.slab[d]] = a.q[(uint32_t)c * a.N + i];
 }
 
-// Workgroups: 64 x 4 columns marching through kZC planes (the z neighbours of a plane are read
+// Workgroups: 64 x 4 columns marching through zc planes (the z neighbours of a plane are read
 // again from the caches by the same threads), numbered XCD-major: the hardware deals consecutive
 // workgroups to the 8 XCDs in turn, so logical workgroup L = xcd_major(w) gives each XCD (one L2)
 // a contiguous range of bricks.
-constexpr int kZC = 16;
 constexpr uint32_t kNumXcd = 8;
 __device__ __forceinline__ uint32_t xcd_major(uint32_t w, uint32_t nb) {
   const uint32_t c = w % kNumXcd, i = w / kNumXcd, q = nb / kNumXcd, r = nb % kNumXcd;
@@ -288,24 +271,140 @@ struct Brick {
   uint32_t L;
 };
 template <typename T>
-__device__ __forceinline__ Brick brick(const PA<T>& a) {
+__device__ __forceinline__ Brick brick(const PA<T>& a, int zc) {
   const uint32_t gx = (uint32_t)(a.n[0] + kBXp - 1) / kBXp, gy = (uint32_t)(a.n[1] + kBYp - 1) / kBYp;
   const uint32_t L = xcd_major(blockIdx.x, gridDim.x);
   const uint32_t bz = L / (gx * gy), r = L - bz * gx * gy, by = r / gx, bx = r - by * gx;
   Brick b;
   b.x = (int)bx * kBXp + threadIdx.x;
   b.y = (int)by * kBYp + threadIdx.y;
-  b.z0 = (int)bz * kZC;
-  b.z1 = min(b.z0 + kZC, a.n[2]);
+  b.z0 = (int)bz * zc;
+  b.z1 = min(b.z0 + zc, a.n[2]);
   b.L = L;
   return b;
 }
 
-// The 12 AT gradients of u, v, w, T at every point; with `publish`, the points on the face layers
+// Derivative of a line at the PE-local index l (PE edge e), at(o) its value at offset o: central
+// (1,4) for 2 <= l <= e - 3, else the standard fourth-order one-sided (l = 0, e - 1) and biased
+// (l = 1, e - 2) stencils.
+template <typename T, typename F>
+__device__ __forceinline__ T line_d1(F at, int l, int e, T i12h) {
+  T s;
+  if (l >= 2 && l <= e - 3) {
+    s = (at(-2) - T(8) * at(-1)) + (T(8) * at(1) - at(2));
+  } else if (l == 0) {
+    s = ((T(-25) * at(0) + T(48) * at(1)) - T(36) * at(2)) + (T(16) * at(3) - T(3) * at(4));
+  } else if (l == 1) {
+    s = ((T(-3) * at(-1) - T(10) * at(0)) + T(18) * at(1)) + (T(-6) * at(2) + at(3));
+  } else if (l == e - 2) {
+    s = ((T(3) * at(1) + T(10) * at(0)) - T(18) * at(-1)) + (T(6) * at(-2) - at(-3));
+  } else {
+    s = ((T(25) * at(0) - T(48) * at(-1)) + T(36) * at(-2)) + (T(-16) * at(-3) + T(3) * at(-4));
+  }
+  return s * i12h;
+}
+
+// The five-point window of the PE-local first derivative at local index l of a PE of edge e (the
+// stencils of line_d1): its case (0 central, 1 l = 0, 2 l = 1, 3 l = e - 2, 4 l = e - 1), whose
+// row of kLineCoef holds the numerators, and its first offset.
+__device__ __forceinline__ int line_case(int l, int e) {
+  return l >= 2 && l <= e - 3 ? 0 : (l == 0 ? 1 : (l == 1 ? 2 : (l == e - 2 ? 3 : 4)));
+}
+__device__ __forceinline__ int line_first(int cs) {
+  return cs == 0 ? -2 : (cs == 1 ? 0 : (cs == 2 ? -1 : (cs == 3 ? -3 : -4)));
+}
+__device__ __forceinline__ double line_coef(int cs, int j) {
+  constexpr double k[5][5] = {{1, -8, 0, 8, -1},
+                              {-25, 48, -36, 16, -3},
+                              {-3, -10, 18, -6, 1},
+                              {-1, 6, -18, 10, 3},
+                              {3, -16, 36, -48, 25}};
+  return k[cs][j];
+}
+
+// Gradient components whose PE-local lines the mixed derivatives take along x (dv/dy, dw/dz,
+// du/dy, du/dz), along y (dv/dx, du/dx, dw/dz, dw/dy) and along z (du/dx, dv/dy, dw/dx, dw/dy).
+__host__ __device__ constexpr int kGx(int c) { return c == 0 ? 4 : (c == 1 ? 8 : (c == 2 ? 1 : 2)); }
+__host__ __device__ constexpr int kGy(int c) { return c == 0 ? 3 : (c == 1 ? 0 : (c == 2 ? 8 : 5)); }
+__host__ __device__ constexpr int kGz(int c) { return c == 0 ? 0 : (c == 1 ? 4 : (c == 2 ? 6 : 7)); }
+
+// The sums of the averaged mixed derivatives, mix[c] = sum over k != c of d/dx_c du_k/dx_k: the mean of
+// the PE-local derivative along x_c of du_k/dx_k and along x_k of du_k/dx_c.  Bound by the caches (9
+// gradient words read and 3 written per point, 40 line values through L1): x and y lines through a
+// window whose offset and numerators are the column's (no divergent branches), z lines from a ring of
+// nine planes in LDS that each thread keeps for its own column (no barriers).  A launch of its own
+// leaves kp_rhs half the registers and a third of the LDS, so twice the waves: 7.5 ms for both at
+// 512^3 FP32 when kp_rhs formed the lines itself at 2 waves per SIMD.
+constexpr int kTG = 4, kTRing = 2 * kTG + 1;
+template <typename T>
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_mixed(PA<T> a) {
+  __shared__ T s_gz[kTRing][4][kBXp * kBYp];  // gradients kGz of planes z - 4 .. z + 4 (slot by plane)
+  const Brick b = brick(a, a.zcm);
+  if (b.x >= a.n[0] || b.y >= a.n[1]) return;
+  const int tid = threadIdx.y * kBXp + threadIdx.x, nz = a.n[2], ez = a.e[2];
+  const int cx = line_case(b.x % a.e[0], a.e[0]), cy = line_case(b.y % a.e[1], a.e[1]);
+  const uint32_t plane = (uint32_t)a.n[0] * a.n[1], col = (uint32_t)b.y * a.n[0] + b.x;
+  const uint32_t ox = (uint32_t)line_first(cx), oy = (uint32_t)(line_first(cy) * a.n[0]);
+  T kx[5], ky[5];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    kx[j] = (T)line_coef(cx, j);
+    ky[j] = (T)line_coef(cy, j);
+  }
+  auto fetch = [&](int z, T g[4]) {  // the kGz gradients of a plane up to 8 planes outside the grid
+    while (z < 0) z += nz;
+    while (z >= nz) z -= nz;
+    const uint32_t i = (uint32_t)z * plane + col;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) g[c] = a.grad[(uint32_t)kGz(c) * a.N + i];
+  };
+  for (int o = -kTG; o < kTG; ++o) {
+    T g[4];
+    fetch(b.z0 + o, g);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s_gz[o + kTG][c][tid] = g[c];
+  }
+  T gn[4];
+  fetch(b.z0 + kTG, gn);
+  int lz = b.z0 % ez, s0 = kTG;  // index of plane z in its z-PE, its ring slot
+  auto slot = [&](int o) {
+    const int t = s0 + o;
+    return t < 0 ? t + kTRing : (t >= kTRing ? t - kTRing : t);
+  };
+  for (int z = b.z0; z < b.z1; ++z) {
+    const uint32_t i = (uint32_t)z * plane + col;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s_gz[slot(kTG)][c][tid] = gn[c];
+    if (z + 1 < b.z1) fetch(z + 1 + kTG, gn);
+    T dx[4], dy[4], dz[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const T* gx = a.grad + ((uint32_t)kGx(c) * a.N + i + ox);
+      const T* gy = a.grad + ((uint32_t)kGy(c) * a.N + i + oy);
+      T sx = kx[0] * gx[0], sy = ky[0] * gy[0];
+#pragma unroll
+      for (int j = 1; j < 5; ++j) {
+        sx += kx[j] * gx[j];
+        sy += ky[j] * gy[(size_t)j * a.n[0]];
+      }
+      dx[c] = sx * a.i12h[0];
+      dy[c] = sy * a.i12h[1];
+      dz[c] = line_d1<T>([&](int o) { return s_gz[slot(o)][c][tid]; }, lz, ez, a.i12h[2]);
+    }
+    // dx: G4 G8 G1 G2; dy: G3 G0 G8 G5; dz: G0 G4 G6 G7
+    a.mix[i] = T(0.5) * (dx[0] + dy[0]) + T(0.5) * (dx[1] + dz[2]);
+    a.mix[a.N + i] = T(0.5) * (dy[1] + dx[2]) + T(0.5) * (dy[2] + dz[3]);
+    a.mix[2 * a.N + i] = T(0.5) * (dz[0] + dx[3]) + T(0.5) * (dz[1] + dy[3]);
+    s0 = slot(1);
+    if (++lz == ez) lz = 0;
+  }
+}
+
+// The nine AT gradients of u, v, w at every point; with `publish`, the points on the face layers
 // also write their conserved variables into ring slot a.slot (stage 1 of a step).
 template <typename T>
 __global__ __launch_bounds__(256) void kp_grad(PA<T> a, int publish) {
-  const Brick b = brick(a);
+  const Brick b = brick(a, a.zc);
   if (b.x >= a.n[0] || b.y >= a.n[1]) return;
   for (int z = b.z0; z < b.z1; ++z) {
     const int p[3] = {b.x, b.y, z};
@@ -313,7 +412,7 @@ __global__ __launch_bounds__(256) void kp_grad(PA<T> a, int publish) {
     const uint32_t i = ((uint32_t)z * a.n[1] + b.y) * a.n[0] + b.x;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-      T g[4] = {T(0), T(0), T(0), T(0)};
+      T g[3] = {T(0), T(0), T(0)};
       const T c1[4] = {T(1), T(-8), T(8), T(-1)};
       const int off[4] = {-2, -1, 1, 2};
 #pragma unroll
@@ -321,10 +420,10 @@ __global__ __launch_bounds__(256) void kp_grad(PA<T> a, int publish) {
         T v[10];
         seen(a, p, tile, d, off[s], v);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) g[c] += c1[s] * v[c];
+        for (int c = 0; c < 3; ++c) g[c] += c1[s] * v[c];
       }
 #pragma unroll
-      for (int c = 0; c < 4; ++c) a.grad[(uint32_t)(c < 3 ? 3 * c + d : 9 + d) * a.N + i] = g[c] * a.i12h[d];
+      for (int c = 0; c < 3; ++c) a.grad[(uint32_t)(3 * c + d) * a.N + i] = g[c] * a.i12h[d];
     }
     if (publish) {
 #pragma unroll
@@ -343,7 +442,7 @@ __global__ __launch_bounds__(256) void kp_grad(PA<T> a, int publish) {
 // Every term of the right-hand side at one point per thread and plane, then the update.
 template <typename T>
 __global__ __launch_bounds__(256) void kp_rhs(PA<T> a) {
-  const Brick b = brick(a);
+  const Brick b = brick(a, a.zc);
   const bool valid = b.x < a.n[0] && b.y < a.n[1];
   double tsum[5] = {0, 0, 0, 0, 0};
   for (int z = b.z0; valid && z < b.z1; ++z) {
@@ -355,7 +454,7 @@ __global__ __launch_bounds__(256) void kp_rhs(PA<T> a) {
     for (int c = 0; c < 5; ++c) qc[c] = a.q[(uint32_t)c * a.N + i];
     derive(a, qc, 0, vc);
     T cont = T(0), conve = T(0), lapT = T(0), conv[3] = {T(0), T(0), T(0)}, lap[3] = {T(0), T(0), T(0)},
-      pg[3], pure[3];
+      pg[3], pure[3], G[12];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       // the first-derivative rows (1, -8, 8, -1) / 12h and the second-derivative rows
@@ -363,7 +462,8 @@ __global__ __launch_bounds__(256) void kp_rhs(PA<T> a) {
       const T c1[4] = {T(1), T(-8), T(8), T(-1)}, c2[4] = {T(-1), T(16), T(16), T(-1)};
       const int off[4] = {-2, -1, 1, 2};
       T s1[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};  // m_d, uu_0d, uu_1d, uu_2d, eu_d, p
-      T s2[4] = {T(0), T(0), T(0), T(0)};              // u, v, w, T
+      T s2[4] = {T(0), T(0), T(0), T(0)};              // u, v, w, T: second derivatives
+      T s3[4] = {T(0), T(0), T(0), T(0)};              // and first ones
 #pragma unroll 1  // one neighbour at a time: 116 VGPRs in FP32 (4 waves per SIMD) against 229 unrolled
       for (int s = 0; s < 4; ++s) {
         T v[10];
@@ -372,7 +472,10 @@ __global__ __launch_bounds__(256) void kp_rhs(PA<T> a) {
         for (int c = 0; c < 5; ++c) s1[c] += c1[s] * v[5 + c];
         s1[5] += c1[s] * v[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) s2[c] += c2[s] * v[c];
+        for (int c = 0; c < 4; ++c) {
+          s2[c] += c2[s] * v[c];
+          s3[c] += c1[s] * v[c];
+        }
       }
       cont += s1[0] * a.i12h[d];
 #pragma unroll
@@ -385,19 +488,12 @@ __global__ __launch_bounds__(256) void kp_rhs(PA<T> a) {
       conve += s1[4] * a.i12h[d];
       pg[d] = s1[5] * a.i12h[d];
       lapT += (s2[3] - T(30) * vc[3]) * a.i12h2[d];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) G[c < 3 ? 3 * c + d : 9 + d] = s3[c] * a.i12h[d];
     }
-    T G[12];
+    T mixed[3];
 #pragma unroll
-    for (int c = 0; c < 12; ++c) G[c] = a.grad[(uint32_t)c * a.N + i];
-    const int loc[3] = {b.x % a.e[0], b.y % a.e[1], z % a.e[2]};
-    T mixed[3];  // sum over k != c of the averaged mixed derivatives d/dx_c du_k/dx_k
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      mixed[c] = T(0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k)
-        if (k != c) mixed[c] += T(0.5) * (pe_d1(a, 3 * k + k, c, i, loc[c]) + pe_d1(a, 3 * k + c, k, i, loc[k]));
-    }
+    for (int c = 0; c < 3; ++c) mixed[c] = a.mix[(uint32_t)c * a.N + i];
     T rhs[5];
     assemble(a, vc, G, cont, conv, conve, pg, lap, lapT, pure, mixed, rhs);
     update_point(a, i, qc, rhs, tsum);
@@ -406,37 +502,38 @@ __global__ __launch_bounds__(256) void kp_rhs(PA<T> a) {
   block_totals(a, tsum, b.L, threadIdx.y * kBXp + threadIdx.x);
 }
 
-// Tiled kernels, for PEs whose x and y edges are multiples of kTB: a workgroup owns a kTB x kTB
-// column tile inside one PE and marches it through kTZ planes.  Per plane, the tile's points and
-// their 2-wide x and y halos are written once to LDS as the differentiated functions that the
-// tile's PE sees (a halo point behind a delayed face of that PE is the extrapolation of its ring
-// levels, as `seen` forms it), so every x and y stencil reads LDS; each column keeps a five-plane
-// register window of its own planes for the z stencils.  kp_rhs_tile also stages the PE-local
-// lines of the gradients that the mixed derivatives differentiate: along x and y in 4-wide halos
-// (the one-sided stencils reach 4 points), along z in a nine-plane LDS ring.
+// Tiled kernels, for PEs whose x and y edges fill tiles of up to kTB x kTB columns well (paper_tile): a
+// workgroup owns a column tile inside one PE and marches it through tz planes.  A PE's face is cut into
+// equal tiles, the last of a row or column maybe narrower; threads outside a narrower tile only help
+// with its halo.  Per plane, the tile's points and their 2-wide x and y halos are written once to LDS
+// as the differentiated functions that the tile's PE sees (a halo point behind a delayed face of that
+// PE is the extrapolation of its ring levels, as `seen` forms it), so every x and y stencil reads LDS;
+// each column keeps a five-plane register window of its own planes for the z stencils.
 //
-// The march is software-pipelined: what plane z + 1 needs from memory (the column's plane z + 3
-// or z + 4, the halo points, the gradients and the register dQ) is fetched while plane z is
-// computed, after the last use of the registers it refills, and consumed after the plane's second
-// barrier.  Loads complete in order, so the compute phase issues no loads of its own (only the
-// planes next to a delayed z face fetch their ring levels there).
-constexpr int kTB = 16, kTZ = 64, kTH = 2, kTG = 4, kTRing = 2 * kTG + 1;
+// The march is software-pipelined: what plane z + 1 needs before its barrier (the column's plane z + 3
+// and the halo points) is fetched while plane z is computed, after the last use of the registers it
+// refills, and consumed after the plane's second barrier; kp_rhs_tile issues what a plane's update
+// needs (mixed sums, register) at its head, behind those.
+constexpr int kTB = 16, kTZ = 64, kTH = 2;
 constexpr int kMaxZPe = kTZ / 5 + 2;  // z-PEs a chunk can touch (PE edges are at least 5)
 
 struct TBrick {
-  int x0, y0, z0, z1;
+  int x0, y0, z0, z1, w, h;
   uint32_t L;
 };
 template <typename T>
 __device__ __forceinline__ TBrick tbrick(const PA<T>& a) {
-  const uint32_t gx = (uint32_t)a.n[0] / kTB, gy = (uint32_t)a.n[1] / kTB;
+  const uint32_t gx = (uint32_t)(a.p[0] * a.tn[0]), gy = (uint32_t)(a.p[1] * a.tn[1]);
   const uint32_t L = xcd_major(blockIdx.x, gridDim.x);
   const uint32_t bz = L / (gx * gy), r = L - bz * gx * gy, by = r / gx, bx = r - by * gx;
   TBrick b;
-  b.x0 = (int)bx * kTB;
-  b.y0 = (int)by * kTB;
-  b.z0 = (int)bz * kTZ;
-  b.z1 = min(b.z0 + kTZ, a.n[2]);
+  const int tx = (int)bx / a.tn[0], ty = (int)by / a.tn[1];  // PE
+  b.x0 = tx * a.e[0] + ((int)bx - tx * a.tn[0]) * a.tw[0];
+  b.y0 = ty * a.e[1] + ((int)by - ty * a.tn[1]) * a.tw[1];
+  b.w = min(a.tw[0], (tx + 1) * a.e[0] - b.x0);
+  b.h = min(a.tw[1], (ty + 1) * a.e[1] - b.y0);
+  b.z0 = (int)bz * a.tz;
+  b.z1 = min(b.z0 + a.tz, a.n[2]);
   b.L = L;
   return b;
 }
@@ -456,7 +553,7 @@ __device__ __forceinline__ void load_delays(const PA<T>& a, const TBrick& b, int
   }
 }
 
-// A halo point of the tile's 2-wide x (d = 0) or y (d = 1) halo, h in [0, 4 kTB): the row (or
+// A halo point of the tile's 2-wide x (d = 0) or y (d = 1) halo, h in [0, 4 side): the row (or
 // column) h / 4 of the tile and the offset m in {-2, -1, +1, +2} from the tile's edge point of it;
 // `pt` the halo point itself (x, y; wrapped), `lds` its index along d in the LDS plane, `face` the
 // face of the tile's PE it lies behind (2 d or 2 d + 1) and `out` whether it does (outside the PE).
@@ -465,15 +562,16 @@ struct Halo {
   bool out;
 };
 template <typename T>
-__device__ __forceinline__ Halo halo_of(const PA<T>& a, int d, int h, int x0, int y0) {
+__device__ __forceinline__ Halo halo_of(const PA<T>& a, int d, int h, const TBrick& b) {
   Halo o;
   o.along = h / 4;
   const int j = h % 4;
   o.m = j < 2 ? j - 2 : j - 1;
-  o.lds = j < 2 ? j : kTB + j;
+  const int x0 = b.x0, y0 = b.y0, side = d == 0 ? b.w : b.h;
+  o.lds = j < 2 ? j : side + j;
   // (selects in place of indexing by d, which would put the arrays in scratch)
   const int e = d == 0 ? a.e[0] : a.e[1], n = d == 0 ? a.n[0] : a.n[1];
-  const int edge = (d == 0 ? x0 : y0) + (j < 2 ? 0 : kTB - 1);
+  const int edge = (d == 0 ? x0 : y0) + (j < 2 ? 0 : side - 1);
   const int le = edge % e + o.m;
   o.out = le < 0 || le >= e;
   o.face = 2 * d + (o.m < 0 ? 0 : 1);
@@ -559,15 +657,16 @@ __device__ __forceinline__ void publish_point(const PA<T>& a, const int p[3], co
   }
 }
 
-// Halo role of a thread: threads [0, 4 kTB) the x halo, [4 kTB, 8 kTB) the y halo.
+// Halo role of a thread: threads [0, 4 kTB) the x halo, [4 kTB, 8 kTB) the y halo, a row (column) of
+// the tile to four.
 struct HaloRole {
   bool on;
   int d;
 };
-__device__ __forceinline__ HaloRole halo_role(int tid) {
+__device__ __forceinline__ HaloRole halo_role(int tid, const TBrick& b) {
   HaloRole r;
-  r.on = tid < 8 * kTB;
   r.d = tid < 4 * kTB ? 0 : 1;
+  r.on = tid < (r.d == 0 ? 4 * b.h : 4 * kTB + 4 * b.w);
   return r;
 }
 
@@ -579,20 +678,21 @@ __device__ __forceinline__ int halo_k(const int (*s_kd)[6], int zl, const Halo& 
 template <typename T>
 __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T> a, int publish) {
   constexpr int LW = kTB + 2 * kTH;
-  __shared__ T s_u[4][LW][LW];  // u, v, w, T of the plane, tile and x / y halos (corners unused)
+  __shared__ T s_u[3][LW][LW];  // u, v, w of the plane, tile and x / y halos (corners unused)
   __shared__ int s_kd[kMaxZPe][6];
   const TBrick b = tbrick(a);
   const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * kTB + tx;
-  const int x = b.x0 + tx, y = b.y0 + ty;
+  const bool act = tx < b.w && ty < b.h;
+  const int x = b.x0 + min(tx, b.w - 1), y = b.y0 + min(ty, b.h - 1);
   const int nz = a.n[2], ez = a.e[2];
-  const HaloRole hr = halo_role(tid);
-  const Halo h = halo_of(a, hr.d, hr.on ? tid - 4 * kTB * hr.d : 0, b.x0, b.y0);
+  const HaloRole hr = halo_role(tid, b);
+  const Halo h = halo_of(a, hr.d, hr.on ? tid - 4 * kTB * hr.d : 0, b);
   load_delays(a, b, s_kd, tid);
   __syncthreads();
 
   // prologue: the window (planes z0 - 2 .. z0 + 2), the published planes among them, plane z0 in
   // LDS, then the fetches for plane z0 + 1
-  T win[4][5];
+  T win[3][5];
 #pragma unroll
   for (int j = 0; j < 5; ++j) {
     const int zz = b.z0 - 2 + j;
@@ -600,14 +700,16 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T
     load_q(a, x, y, wrapi(zz, nz), q);
     derive(a, q, 0, v);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) win[c][j] = v[c];
-    if (publish && zz >= b.z0 && zz < b.z1) {
+    for (int c = 0; c < 3; ++c) win[c][j] = v[c];
+    if (publish && act && zz >= b.z0 && zz < b.z1) {
       const int p[3] = {x, y, zz};
       publish_point(a, p, q);
     }
   }
+  if (act) {
 #pragma unroll
-  for (int c = 0; c < 4; ++c) s_u[c][ty + kTH][tx + kTH] = win[c][2];
+    for (int c = 0; c < 3; ++c) s_u[c][ty + kTH][tx + kTH] = win[c][2];
+  }
   Raw<T> hw;
   int hk = 0;
   if (hr.on) {
@@ -616,7 +718,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T
     T v[10];
     finish_raw(a, hr.d, hk, hw, v);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
+    for (int c = 0; c < 3; ++c) {
       if (hr.d == 0) s_u[c][h.along + kTH][h.lds] = v[c];
       else s_u[c][h.lds][h.along + kTH] = v[c];
     }
@@ -634,11 +736,11 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T
     const uint32_t i = ((uint32_t)z * a.n[1] + y) * a.n[0] + x;
     const T c1[4] = {T(1), T(-8), T(8), T(-1)};
     const int off[4] = {-2, -1, 1, 2};
-    T gx[4] = {T(0), T(0), T(0), T(0)}, gy[4] = {T(0), T(0), T(0), T(0)}, gz[4] = {T(0), T(0), T(0), T(0)};
+    T gx[3] = {T(0), T(0), T(0)}, gy[3] = {T(0), T(0), T(0)}, gz[3] = {T(0), T(0), T(0)};
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < 3; ++c) {
         gx[c] += c1[s] * s_u[c][ty + kTH][tx + kTH + off[s]];
         gy[c] += c1[s] * s_u[c][ty + kTH + off[s]][tx + kTH];
       }
@@ -647,7 +749,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) gz[c] += c1[s] * win[c][2 + off[s]];
+        for (int c = 0; c < 3; ++c) gz[c] += c1[s] * win[c][2 + off[s]];
     } else {
       const int p[3] = {x, y, z};
       const int pe = pe_of(a, b.x0, b.y0, z);
@@ -656,15 +758,17 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T
         T v[10];
         seen(a, p, pe, 2, off[s], v);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) gz[c] += c1[s] * v[c];
+        for (int c = 0; c < 3; ++c) gz[c] += c1[s] * v[c];
       }
     }
+    if (act) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {  // streamed out (read by the next launch)
-      const uint32_t g0 = (uint32_t)(c < 3 ? 3 * c : 9);
-      __builtin_nontemporal_store(gx[c] * a.i12h[0], a.grad + (g0 + 0) * a.N + i);
-      __builtin_nontemporal_store(gy[c] * a.i12h[1], a.grad + (g0 + 1) * a.N + i);
-      __builtin_nontemporal_store(gz[c] * a.i12h[2], a.grad + (g0 + 2) * a.N + i);
+      for (int c = 0; c < 3; ++c) {  // streamed out (read by the next launch)
+        const uint32_t g0 = (uint32_t)(3 * c);
+        __builtin_nontemporal_store(gx[c] * a.i12h[0], a.grad + (g0 + 0) * a.N + i);
+        __builtin_nontemporal_store(gy[c] * a.i12h[1], a.grad + (g0 + 1) * a.N + i);
+        __builtin_nontemporal_store(gz[c] * a.i12h[2], a.grad + (g0 + 2) * a.N + i);
+      }
     }
     __syncthreads();
     if (z + 1 < b.z1) {  // uniform
@@ -673,23 +777,25 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T
         T v[10];
         derive(a, qn, 0, v);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < 3; ++c) {
 #pragma unroll
           for (int j = 0; j < 4; ++j) win[c][j] = win[c][j + 1];
           win[c][4] = v[c];
         }
-        if (publish && z + 3 < b.z1) {
+        if (publish && act && z + 3 < b.z1) {
           const int p[3] = {x, y, z + 3};
           publish_point(a, p, qn);
         }
       }
+      if (act) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) s_u[c][ty + kTH][tx + kTH] = win[c][2];
+        for (int c = 0; c < 3; ++c) s_u[c][ty + kTH][tx + kTH] = win[c][2];
+      }
       if (hr.on) {
         T v[10];
         finish_raw(a, hr.d, hk, hw, v);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < 3; ++c) {
           if (hr.d == 0) s_u[c][h.along + kTH][h.lds] = v[c];
           else s_u[c][h.lds][h.along + kTH] = v[c];
         }
@@ -708,142 +814,49 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) void kp_grad_tile(PA<T
   }
 }
 
-// Derivative of a line at the PE-local index l (PE edge e), at(o) its value at offset o, with the
-// stencils of pe_d1.
-template <typename T, typename F>
-__device__ __forceinline__ T line_d1(F at, int l, int e, T i12h) {
-  T s;
-  if (l >= 2 && l <= e - 3) {
-    s = (at(-2) - T(8) * at(-1)) + (T(8) * at(1) - at(2));
-  } else if (l == 0) {
-    s = ((T(-25) * at(0) + T(48) * at(1)) - T(36) * at(2)) + (T(16) * at(3) - T(3) * at(4));
-  } else if (l == 1) {
-    s = ((T(-3) * at(-1) - T(10) * at(0)) + T(18) * at(1)) + (T(-6) * at(2) + at(3));
-  } else if (l == e - 2) {
-    s = ((T(3) * at(1) + T(10) * at(0)) - T(18) * at(-1)) + (T(6) * at(-2) - at(-3));
-  } else {
-    s = ((T(25) * at(0) - T(48) * at(-1)) + T(36) * at(-2)) + (T(-16) * at(-3) + T(3) * at(-4));
-  }
-  return s * i12h;
-}
-
-// The five-point window of the PE-local first derivative at local index l of a PE of edge e (the
-// stencils of pe_d1): its case (0 central, 1 l = 0, 2 l = 1, 3 l = e - 2, 4 l = e - 1), whose
-// row of kLineCoef holds the numerators, and its first offset.
-__device__ __forceinline__ int line_case(int l, int e) {
-  return l >= 2 && l <= e - 3 ? 0 : (l == 0 ? 1 : (l == 1 ? 2 : (l == e - 2 ? 3 : 4)));
-}
-__device__ __forceinline__ int line_first(int cs) {
-  return cs == 0 ? -2 : (cs == 1 ? 0 : (cs == 2 ? -1 : (cs == 3 ? -3 : -4)));
-}
-__device__ __forceinline__ double line_coef(int cs, int j) {
-  constexpr double k[5][5] = {{1, -8, 0, 8, -1},
-                              {-25, 48, -36, 16, -3},
-                              {-3, -10, 18, -6, 1},
-                              {-1, 6, -18, 10, 3},
-                              {3, -16, 36, -48, 25}};
-  return k[cs][j];
-}
-
-// Gradient components whose PE-local lines the mixed derivatives take along x (dv/dy, dw/dz,
-// du/dy, du/dz), along y (dv/dx, du/dx, dw/dz, dw/dy) and along z (du/dx, dv/dy, dw/dx, dw/dy).
-__host__ __device__ constexpr int kGx(int c) { return c == 0 ? 4 : (c == 1 ? 8 : (c == 2 ? 1 : 2)); }
-__host__ __device__ constexpr int kGy(int c) { return c == 0 ? 3 : (c == 1 ? 0 : (c == 2 ? 8 : 5)); }
-__host__ __device__ constexpr int kGz(int c) { return c == 0 ? 0 : (c == 1 ? 4 : (c == 2 ? 6 : 7)); }
-// the tile's own gradients that go to the x / y line planes: 0, 1, 2, 3, 4, 5, 8
-__host__ __device__ constexpr int kGo(int c) { return c < 6 ? c : 8; }
-
 template <typename T>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void kp_rhs_tile(PA<T> a) {
-  constexpr int LW = kTB + 2 * kTH, GW = kTB + 2 * kTG, NP = kTB * kTB;
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 1) void kp_rhs_tile(PA<T> a) {
+  constexpr int LW = kTB + 2 * kTH;
   __shared__ T s_u[5][LW][LW];         // u, v, w, T, p: tile and x / y halos (corners unused)
   __shared__ T s_fx[5][kTB][LW];       // m_x, m_i u, rho e u on the tile rows with the x halo
   __shared__ T s_fy[5][LW][kTB];       // m_y, m_i v, rho e v on the tile columns with the y halo
-  __shared__ T s_gx[4][kTB][GW];       // gradients kGx on the tile rows, x halo 4
-  __shared__ T s_gy[4][GW][kTB];       // gradients kGy on the tile columns, y halo 4
-  __shared__ T s_gz[kTRing][4][NP];    // gradients kGz of planes z - 4 .. z + 4 (slot by plane)
   __shared__ int s_kd[kMaxZPe][6];
-  __shared__ T s_lc[5][5];             // line stencil numerators by case
   const TBrick b = tbrick(a);
   const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * kTB + tx;
-  const int x = b.x0 + tx, y = b.y0 + ty;
-  // this thread's PE-local x and y line windows (fixed for the march): case and first offset
-  const int cxs = line_case(x % a.e[0], a.e[0]), cys = line_case(y % a.e[1], a.e[1]);
-  const int ox = line_first(cxs), oy = line_first(cys);
-  if (tid < 25) s_lc[tid / 5][tid % 5] = (T)line_coef(tid / 5, tid % 5);
+  const bool act = tx < b.w && ty < b.h;
+  const int x = b.x0 + min(tx, b.w - 1), y = b.y0 + min(ty, b.h - 1);
   const int nz = a.n[2], ez = a.e[2];
   const bool need_dq = a.rk_a != T(0) || a.c_prev != T(0);
-  const HaloRole hr = halo_role(tid);
-  const Halo h = halo_of(a, hr.d, hr.on ? tid - 4 * kTB * hr.d : 0, b.x0, b.y0);
-  // this thread's point of the 4-wide gradient halos: x (tid < 8 kTB), then y
-  const int gd = tid < 8 * kTB ? 0 : 1, gh = tid - 8 * kTB * gd, galong = gh / 8, gj = gh % 8;
-  const int gl = gj < 4 ? gj : kTB + gj;
-  const int ghx = gd == 0 ? wrapi(b.x0 + (gj < 4 ? gj - 4 : kTB + gj - 4), a.n[0]) : b.x0 + galong;
-  const int ghy = gd == 0 ? b.y0 + galong : wrapi(b.y0 + (gj < 4 ? gj - 4 : kTB + gj - 4), a.n[1]);
-  auto gidx = [&](int xx, int yy, int zz) {  // zz may lie a few planes outside the grid
-    int zw = zz;
-    while (zw < 0) zw += nz;
-    while (zw >= nz) zw -= nz;
-    return ((uint32_t)zw * a.n[1] + yy) * a.n[0] + xx;
-  };
-  auto ring_add = [](int sl, int o) {  // ring slot o planes from slot sl, |o| < kTRing
-    const int t = sl + o;
-    return t < 0 ? t + kTRing : (t >= kTRing ? t - kTRing : t);
-  };
+  const HaloRole hr = halo_role(tid, b);
+  const Halo h = halo_of(a, hr.d, hr.on ? tid - 4 * kTB * hr.d : 0, b);
   load_delays(a, b, s_kd, tid);
 
-  // plane-z registers and the fetches for the next plane
   T wq[5][5];  // conserved variables of the column's planes z - 2 .. z + 2
-  T dqc[5], gT[3];
-  T qn[5], gon[7], grn[4], ghn[4], dqn[5], gTn[3];
-  Raw<T> hw;
+  T qn[5];     // the column's next plane
+  Raw<T> hw;   // the halo point of the next plane
   int hk = 0;
 
   // prologue
 #pragma unroll
   for (int j = 0; j < 5; ++j) load_q(a, x, y, wrapi(b.z0 - 2 + j, nz), wq[j]);
-  for (int zz = b.z0 - kTG; zz <= b.z0 + kTG; ++zz) {
-    const uint32_t iz = gidx(x, y, zz);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) s_gz[zz - b.z0 + kTG][c][tid] = a.grad[(uint32_t)kGz(c) * a.N + iz];
-  }
-  {
-    const uint32_t i0 = gidx(x, y, b.z0), ih = gidx(ghx, ghy, b.z0);
-#pragma unroll
-    for (int c = 0; c < 7; ++c) gon[c] = a.grad[(uint32_t)kGo(c) * a.N + i0];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) ghn[c] = a.grad[(uint32_t)(gd == 0 ? kGx(c) : kGy(c)) * a.N + ih];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) gT[c] = a.grad[(uint32_t)(9 + c) * a.N + i0];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) dqc[c] = need_dq ? a.dq[(uint32_t)c * a.N + i0] : T(0);
-  }
   __syncthreads();  // s_kd
   if (hr.on) {
     hk = halo_k(s_kd, 0, h);
     fetch_raw(a, h.pt[0], h.pt[1], b.z0, hr.d, hk, hw);
   }
 
-  // Writes plane zz's own values, halo values and gradient lines to LDS from the registers.
+  // Writes the current plane's own and halo values to LDS from the registers.
   auto stage_plane = [&]() {
-    T vx[10], vy[10];
-    derive(a, wq[2], 0, vx);
-    derive(a, wq[2], 1, vy);
+    if (act) {
+      T vx[10], vy[10];
+      derive(a, wq[2], 0, vx);
+      derive(a, wq[2], 1, vy);
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      s_u[c][ty + kTH][tx + kTH] = vx[c];
-      s_fx[c][ty][tx + kTH] = vx[5 + c];
-      s_fy[c][ty + kTH][tx] = vy[5 + c];
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      // own gradients: kGx = (4, 8, 1, 2), kGy = (3, 0, 8, 5) among kGo = (0, 1, 2, 3, 4, 5, 8)
-      const int ox = c == 0 ? 4 : (c == 1 ? 6 : (c == 2 ? 1 : 2));
-      const int oy = c == 0 ? 3 : (c == 1 ? 0 : (c == 2 ? 6 : 5));
-      s_gx[c][ty][tx + kTG] = gon[ox];
-      s_gy[c][ty + kTG][tx] = gon[oy];
-      if (gd == 0) s_gx[c][galong][gl] = ghn[c];
-      else s_gy[c][gl][galong] = ghn[c];
+      for (int c = 0; c < 5; ++c) {
+        s_u[c][ty + kTH][tx + kTH] = vx[c];
+        s_fx[c][ty][tx + kTH] = vx[5 + c];
+        s_fy[c][ty + kTH][tx] = vy[5 + c];
+      }
     }
     if (hr.on) {
       T v[10];
@@ -860,20 +873,9 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void kp_rhs_tile(PA<T>
       }
     }
   };
-  // Issues the loads for plane zz (the column's plane zz + 2, the ring plane zz + 4).
+  // Issues the loads for plane zz: the column's plane zz + 2 and the halo points.
   auto fetch_plane = [&](int zz, int zzl) {  // zzl: the z-PE of plane zz within the chunk
     load_q(a, x, y, wrapi(zz + 2, nz), qn);
-    const uint32_t io = gidx(x, y, zz), ih = gidx(ghx, ghy, zz), ir = gidx(x, y, zz + kTG);
-#pragma unroll
-    for (int c = 0; c < 7; ++c) gon[c] = a.grad[(uint32_t)kGo(c) * a.N + io];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) ghn[c] = a.grad[(uint32_t)(gd == 0 ? kGx(c) : kGy(c)) * a.N + ih];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) grn[c] = a.grad[(uint32_t)kGz(c) * a.N + ir];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) gTn[c] = a.grad[(uint32_t)(9 + c) * a.N + io];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) dqn[c] = need_dq ? __builtin_nontemporal_load(a.dq + (uint32_t)c * a.N + io) : T(0);
     if (hr.on && zz < b.z1) {
       hk = halo_k(s_kd, zzl, h);
       fetch_raw(a, h.pt[0], h.pt[1], zz, hr.d, hk, hw);
@@ -884,27 +886,37 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void kp_rhs_tile(PA<T>
   fetch_plane(b.z0 + 1, lz0 + 1 >= ez ? 1 : 0);
 
   double tsum[5] = {0, 0, 0, 0, 0};
-  int lz = lz0, zl = 0, s0 = kTG;  // plane z: its index in its z-PE, that z-PE, its ring slot
+  int lz = lz0, zl = 0;  // plane z: its index in its z-PE, that z-PE
   for (int z = b.z0; z < b.z1; ++z) {
     __syncthreads();
     const uint32_t i = ((uint32_t)z * a.n[1] + y) * a.n[0] + x;
+    // what the update of this plane needs, arriving behind the stencils
+    T mixed[3], dqc[5];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) mixed[c] = a.mix[(uint32_t)c * a.N + i];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) dqc[c] = need_dq ? __builtin_nontemporal_load(a.dq + (uint32_t)c * a.N + i) : T(0);
     T vc[10];
     derive(a, wq[2], 0, vc);
     T cont = T(0), conve = T(0), lapT = T(0), conv[3] = {T(0), T(0), T(0)}, lap[3] = {T(0), T(0), T(0)},
-      pg[3], pure[3];
+      pg[3], pure[3], G[12];
     const T c1[4] = {T(1), T(-8), T(8), T(-1)}, c2[4] = {T(-1), T(16), T(16), T(-1)};
     const int off[4] = {-2, -1, 1, 2};
     const bool zface = (lz < 2 && s_kd[zl][4] > 0) || (lz >= ez - 2 && s_kd[zl][5] > 0);  // uniform
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       T s1[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};  // m_d, uu_0d, uu_1d, uu_2d, eu_d, p
-      T s2[4] = {T(0), T(0), T(0), T(0)};              // u, v, w, T
+      T s2[4] = {T(0), T(0), T(0), T(0)};              // u, v, w, T: second derivatives
+      T s3[4] = {T(0), T(0), T(0), T(0)};              // and first ones
       auto acc = [&](int s, const T v[10]) {
 #pragma unroll
         for (int c = 0; c < 5; ++c) s1[c] += c1[s] * v[5 + c];
         s1[5] += c1[s] * v[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) s2[c] += c2[s] * v[c];
+        for (int c = 0; c < 4; ++c) {
+          s2[c] += c2[s] * v[c];
+          s3[c] += c1[s] * v[c];
+        }
       };
       if (d < 2) {
 #pragma unroll 1  // one neighbour at a time from LDS (register pressure)
@@ -947,55 +959,16 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void kp_rhs_tile(PA<T>
       conve += s1[4] * a.i12h[d];
       pg[d] = s1[5] * a.i12h[d];
       lapT += (s2[3] - T(30) * vc[3]) * a.i12h2[d];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) G[c < 3 ? 3 * c + d : 9 + d] = s3[c] * a.i12h[d];
     }
-    // mixed derivatives: d/dx_c du_k/dx_k as the average of the PE-local derivative along x_c of
-    // du_k/dx_k and along x_k of du_k/dx_c (k != c)
-    T dx[4], dy[4], dzl[4];
-    {
-      T kx[5], ky[5];
-#pragma unroll
-      for (int j = 0; j < 5; ++j) {
-        kx[j] = s_lc[cxs][j];
-        ky[j] = s_lc[cys][j];
-      }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        // x and y: the thread's window, branch-free; z: uniform cases
-        T sx = kx[0] * s_gx[c][ty][tx + kTG + ox], sy = ky[0] * s_gy[c][ty + kTG + oy][tx];
-#pragma unroll
-        for (int j = 1; j < 5; ++j) {
-          sx += kx[j] * s_gx[c][ty][tx + kTG + ox + j];
-          sy += ky[j] * s_gy[c][ty + kTG + oy + j][tx];
-        }
-        dx[c] = sx * a.i12h[0];
-        dy[c] = sy * a.i12h[1];
-        dzl[c] = line_d1<T>([&](int o) { return s_gz[ring_add(s0, o)][c][tid]; }, lz, ez, a.i12h[2]);
-      }
-    }
-    // dx: G4 G8 G1 G2; dy: G3 G0 G8 G5; dzl: G0 G4 G6 G7
-    T mixed[3];
-    mixed[0] = T(0.5) * (dx[0] + dy[0]) + T(0.5) * (dx[1] + dzl[2]);
-    mixed[1] = T(0.5) * (dy[1] + dx[2]) + T(0.5) * (dy[2] + dzl[3]);
-    mixed[2] = T(0.5) * (dzl[0] + dx[3]) + T(0.5) * (dzl[1] + dy[3]);
-    T G[12];
-    G[0] = s_gy[1][ty + kTG][tx];
-    G[1] = s_gx[2][ty][tx + kTG];
-    G[2] = s_gx[3][ty][tx + kTG];
-    G[3] = s_gy[0][ty + kTG][tx];
-    G[4] = s_gx[0][ty][tx + kTG];
-    G[5] = s_gy[3][ty + kTG][tx];
-    G[6] = s_gz[s0][2][tid];
-    G[7] = s_gz[s0][3][tid];
-    G[8] = s_gx[1][ty][tx + kTG];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) G[9 + c] = gT[c];
     T rhs[5];
     assemble(a, vc, G, cont, conv, conve, pg, lap, lapT, pure, mixed, rhs);
-    // the update (or the RHS alone), with dQ of this plane from registers
-    if (a.mode == kModeRhsH) {
+    // the update (or the RHS alone)
+    if (act && a.mode == kModeRhsH) {
 #pragma unroll
       for (int c = 0; c < 5; ++c) __builtin_nontemporal_store(rhs[c], a.rhs_out + (uint32_t)c * a.N + i);
-    } else {
+    } else if (act) {
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
         const T prev = dqc[c];
@@ -1013,18 +986,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void kp_rhs_tile(PA<T>
 #pragma unroll
         for (int c = 0; c < 5; ++c) wq[j][c] = wq[j + 1][c];
 #pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        wq[4][c] = qn[c];
-        dqc[c] = dqn[c];
-      }
-#pragma unroll
-      for (int c = 0; c < 3; ++c) gT[c] = gTn[c];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) s_gz[ring_add(s0, kTG + 1)][c][tid] = grn[c];  // plane z + 5
+      for (int c = 0; c < 5; ++c) wq[4][c] = qn[c];
       stage_plane();
       fetch_plane(z + 2, zl + (lz + 2 >= ez ? 1 : 0));
     }
-    s0 = ring_add(s0, 1);
     if (++lz == ez) {
       lz = 0;
       ++zl;
@@ -1032,6 +997,35 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 2 : 1) void kp_rhs_tile(PA<T>
   }
   if (a.mode != kModeStepH) return;  // uniform across the grid
   block_totals(a, tsum, b.L, tid);
+}
+
+// How form 1 cuts a grid: the planes of the point-per-thread bricks and of kp_mixed, and the tiles.
+struct PaperPlan {
+  int zc, zcm, tw[2], tn[2], tz;
+  bool tiled;
+  int64_t brick_blocks, mixed_blocks, tile_blocks;
+};
+int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+PaperPlan paper_plan(const Geom& g) {
+  PaperPlan p{};
+  const int64_t cols = (int64_t)cdiv(g.n[0], kBXp) * cdiv(g.n[1], kBYp);
+  // 16 planes to a brick, or as many fewer as leave 2048 workgroups (8 per compute unit: each plane
+  // is a chain of round trips that other waves have to hide); kp_mixed fills its ring with 8 planes
+  // first, so 64, down to 8
+  p.zc = (int)std::max<int64_t>(1, std::min<int64_t>(16, cols * g.n[2] / 2048));
+  p.zcm = (int)std::max<int64_t>(8, std::min<int64_t>(64, cols * g.n[2] / 2048));
+  p.brick_blocks = cols * cdiv(g.n[2], p.zc);
+  p.mixed_blocks = cols * cdiv(g.n[2], p.zcm);
+  // tiles: a PE's edge in equal parts of at most kTB; worth it where the tile fills half its threads
+  for (int d = 0; d < 2; ++d) {
+    p.tn[d] = cdiv(g.e[d], kTB);
+    p.tw[d] = cdiv(g.e[d], p.tn[d]);
+  }
+  p.tiled = p.tw[0] * p.tw[1] >= kTB * kTB / 2;
+  const int64_t tiles = (int64_t)g.p[0] * p.tn[0] * g.p[1] * p.tn[1];
+  p.tz = (int)std::max<int64_t>(8, std::min<int64_t>(kTZ, tiles * g.n[2] / 1024));
+  p.tile_blocks = tiles * cdiv(g.n[2], p.tz);
+  return p;
 }
 
 template <typename T>
@@ -1042,6 +1036,7 @@ PA<T> pack(const StagePArgs<T>& s) {
   a.q_out = s.q_out;
   a.dq = s.dq;
   a.grad = s.grad;
+  a.mix = s.mode == kModeRhsH ? s.rhs_out : s.q_out;
   a.ring = s.ring;
   a.rhs_out = s.rhs_out;
   a.delays = s.delays;
@@ -1065,6 +1060,14 @@ PA<T> pack(const StagePArgs<T>& s) {
   a.slot = s.slot;
   a.store_dq = s.store_dq;
   a.mode = s.mode;
+  const PaperPlan pl = paper_plan(g);
+  a.zc = pl.zc;
+  a.zcm = pl.zcm;
+  for (int d = 0; d < 2; ++d) {
+    a.tw[d] = pl.tw[d];
+    a.tn[d] = pl.tn[d];
+  }
+  a.tz = pl.tz;
   a.cs = s.cs;
   a.rk_a = s.rk_a;
   a.rk_b = s.rk_b;
@@ -1084,16 +1087,10 @@ PA<T> pack(const StagePArgs<T>& s) {
 
 }  // namespace
 
-bool paper_tiled(const Geom& g) { return g.e[0] % kTB == 0 && g.e[1] % kTB == 0; }
-
-int64_t paper_tiled_blocks(const Geom& g) {
-  return (int64_t)(g.n[0] / kTB) * (g.n[1] / kTB) * ((g.n[2] + kTZ - 1) / kTZ);
-}
-
 // Workgroup slots of the FP64 totals: enough for either kernel.
 int64_t paper_blocks(const Geom& g) {
-  const int64_t pt = (int64_t)((g.n[0] + kBXp - 1) / kBXp) * ((g.n[1] + kBYp - 1) / kBYp) * ((g.n[2] + kZC - 1) / kZC);
-  return paper_tiled(g) ? std::max(pt, paper_tiled_blocks(g)) : pt;
+  const PaperPlan p = paper_plan(g);
+  return p.tiled ? std::max(p.brick_blocks, p.tile_blocks) : p.brick_blocks;
 }
 
 template <typename T>
@@ -1104,17 +1101,18 @@ hipError_t launch_stagep(const StagePArgs<T>& s, int which, hipStream_t stream) 
     hipLaunchKernelGGL((kp_publish<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, a);
     return hipGetLastError();
   }
-  if (paper_tiled(s.g)) {
-    const dim3 grid((unsigned)paper_tiled_blocks(s.g)), block(kTB, kTB);
-    if (which == kPGrad || which == kPGradPublish)
-      hipLaunchKernelGGL((kp_grad_tile<T>), grid, block, 0, stream, a, which == kPGradPublish ? 1 : 0);
-    else hipLaunchKernelGGL((kp_rhs_tile<T>), grid, block, 0, stream, a);
+  const PaperPlan pl = paper_plan(s.g);
+  const dim3 brick(kBXp, kBYp);
+  if (which == kPGrad || which == kPGradPublish) {
+    const int publish = which == kPGradPublish ? 1 : 0;
+    if (pl.tiled)
+      hipLaunchKernelGGL((kp_grad_tile<T>), dim3((unsigned)pl.tile_blocks), dim3(kTB, kTB), 0, stream, a, publish);
+    else hipLaunchKernelGGL((kp_grad<T>), dim3((unsigned)pl.brick_blocks), brick, 0, stream, a, publish);
     return hipGetLastError();
   }
-  const dim3 grid((unsigned)paper_blocks(s.g));
-  if (which == kPGrad || which == kPGradPublish)
-    hipLaunchKernelGGL((kp_grad<T>), grid, dim3(kBXp, kBYp), 0, stream, a, which == kPGradPublish ? 1 : 0);
-  else hipLaunchKernelGGL((kp_rhs<T>), grid, dim3(kBXp, kBYp), 0, stream, a);
+  hipLaunchKernelGGL((kp_mixed<T>), dim3((unsigned)pl.mixed_blocks), brick, 0, stream, a);
+  if (pl.tiled) hipLaunchKernelGGL((kp_rhs_tile<T>), dim3((unsigned)pl.tile_blocks), dim3(kTB, kTB), 0, stream, a);
+  else hipLaunchKernelGGL((kp_rhs<T>), dim3((unsigned)pl.brick_blocks), brick, 0, stream, a);
   return hipGetLastError();
 }
 

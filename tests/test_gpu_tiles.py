@@ -39,7 +39,7 @@ def smooth_levels(n, nlev, seed, form):
 
 
 def check(n, p, order=4, form=0, steps=2, precision="fp64", tol=TOL64, tune=None):
-    nlev = 7
+    nlev = 7 if order == 6 else 6
     q = smooth_levels(n, nlev, sum(n), form)
     kw = dict(n=n, p=p, dt=2e-3, mu_ref=0.02, max_delay=3, order=order, form=form)
     g = atns.Sim(atns.Config(precision=precision, **kw))
@@ -75,3 +75,16 @@ def check(n, p, order=4, form=0, steps=2, precision="fp64", tol=TOL64, tune=None
                                  ((33, 21, 24), (1, 1, 3)), ((130, 9, 12), (2, 1, 1))])
 def test_order6_tiles(n, p):
     check(n, p, order=6)
+
+
+# the paper's form: edges 5 (the smallest PE), 9 and 11 (tiles of 9 x 11 use 99 of 256 threads: a point
+# per thread), 12 and 11 (132: a partial tile), 17 (9 + 8) and 33 (three tiles, z cut into chunks that
+# start inside a PE), grids of fewer columns than a brick
+@pytest.mark.parametrize("n,p", [((10, 5, 15), (2, 1, 3)), ((18, 22, 10), (2, 2, 1)), ((12, 22, 30), (1, 2, 2)),
+                                 ((34, 33, 18), (2, 1, 3)), ((66, 16, 40), (2, 1, 2))])
+def test_paper_form_tiles(n, p):
+    check(n, p, form=1)
+
+
+def test_paper_form_tiles_fp32():
+    check((34, 30, 36), (2, 2, 3), form=1, precision="fp32", tol=2e-6)
