@@ -1,6 +1,8 @@
 // gfx950 support kernels of the AT compressible Navier-Stokes library: FP64 statistics with
 // synchronous 4th-order central derivatives (the k = 0 rows of the (1,4) schemes, Appendix B) and
 // fixed-order reductions, precision conversion, and the separable forcing table.
+#include <algorithm>
+
 #include "atns_internal.h"
 
 namespace atns {
@@ -8,13 +10,6 @@ namespace {
 
 constexpr int kBX = 64;  // one wavefront along x
 constexpr int kBY = 4;
-
-template <typename T>
-__device__ __forceinline__ T tpow(T a, T b);
-template <>
-__device__ __forceinline__ double tpow<double>(double a, double b) { return pow(a, b); }
-template <>
-__device__ __forceinline__ float tpow<float>(float a, float b) { return powf(a, b); }
 
 __device__ __forceinline__ int wrap1(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
@@ -38,83 +33,158 @@ __device__ __forceinline__ double wave_sum(double v) {
 }
 
 // Statistics partials per block with synchronous periodic derivatives (no PE faces) of the run's
-// order: the (1,4) central stencil (M = 2) or the (1,6) one (M = 3).
+// order: the (1,4) central stencil (M = 2) or the (1,6) one (M = 3).  A workgroup marches a 64 x 8
+// column tile through zc planes: each point's primitives are formed once (1.6 times with the halo; 13
+// times, a division each, when every point formed its neighbours' own), x and y neighbours come from
+// an LDS plane (two of them, one barrier a plane), z neighbours from a register window, and the loads
+// of the next plane are issued before the barrier.  256^3 FP64: 0.67 ms with a point per thread.
+constexpr int kSX = 64, kSY = 8;
 template <typename T, int M>
-__global__ __launch_bounds__(256) void k_stats(Geom g, Coef<T> cf, const T* __restrict__ q,
-                                               double* __restrict__ part) {
-  const int x = blockIdx.x * kBX + threadIdx.x;
-  const int y = blockIdx.y * kBY + threadIdx.y;
-  const int z = blockIdx.z;
-  const bool valid = x < g.n[0] && y < g.n[1];
+__global__ __launch_bounds__(kSX* kSY) void k_stats(Geom g, Coef<T> cf, const T* __restrict__ q,
+                                                    double* __restrict__ part, int zc) {
+  constexpr int LW = kSX + 2 * M, LH = kSY + 2 * M;
+  __shared__ T s_u[2][3][LH][LW];
+  __shared__ double red[kSY][kNStat];
+  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+  const int gx = (nx + kSX - 1) / kSX, gy = (ny + kSY - 1) / kSY;
+  const int blk = (int)blockIdx.x, bz = blk / (gx * gy), br = blk - bz * gx * gy, by = br / gx, bx = br - by * gx;
+  const int x0 = bx * kSX, y0 = by * kSY, z0 = bz * zc, z1 = min(z0 + zc, nz);
+  const int w = min(kSX, nx - x0), h = min(kSY, ny - y0);
+  const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * kSX + tx;
+  const bool act = tx < w && ty < h;
+  const int64_t N = g.npts, plane = (int64_t)nx * ny;
+  const int64_t col = (int64_t)(y0 + min(ty, h - 1)) * nx + x0 + min(tx, w - 1);
+  // this thread's halo point of every plane
+  int hl = -1;  // its place in the LDS plane
+  int64_t hcol = col;
+  {
+    int hx = 0, hy = 0;
+    if (tid < 2 * M * h) {
+      const int r = tid / (2 * M), c = tid - r * (2 * M);
+      hx = c < M ? c - M : w + c - M;
+      hy = r;
+    } else if (tid < 2 * M * (h + w)) {
+      const int i = tid - 2 * M * h, r = i / w;
+      hx = i - r * w;
+      hy = r < M ? r - M : h + r - M;
+    }
+    if (tid < 2 * M * (h + w)) {
+      hl = (hy + M) * LW + hx + M;
+      hcol = (int64_t)wrap1(y0 + hy, ny) * nx + wrap1(x0 + hx, nx);
+    }
+  }
   double s[kNStat];
 #pragma unroll
   for (int c = 0; c < kNStat; ++c) s[c] = 0.0;
-  if (valid) {
-    const int64_t N = g.npts;
-    const int64_t i = ((int64_t)z * g.n[1] + y) * g.n[0] + x;
-    const int pt[3] = {x, y, z};
-    T G[kNGrad];
+  T win[3][2 * M + 1], tw[M + 1];  // u, v, w of planes z - M .. z + M; T of planes z .. z + M
+  auto fetch = [&](int64_t c0, int z, T v[5]) {
+    const int64_t i = (int64_t)wrap1(z, nz) * plane + c0;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      T v[2 * M][4];
+    for (int c = 0; c < kNQ; ++c) v[c] = q[c * N + i];
+  };
+  // u, v, w, T of a column's plane; own planes of the chunk add their pointwise sums here
+  auto absorb = [&](const T v[5], bool mine, T pr[5]) {
+    primitives<T>(v, 1, 0, cf.inv_cv, cf.form, pr);
+    if (mine) {
+      const double u = pr[1], vv = pr[2], ww = pr[3];
+      const double uu = u * u + vv * vv + ww * ww;
+      int nonfin = 0;
 #pragma unroll
-      for (int mi = 0; mi < 2 * M; ++mi) {
-        const int m = mi < M ? mi - M : mi - M + 1;
-        int r[3] = {x, y, z};
-        r[d] = wrap1(pt[d] + m, g.n[d]);
-        const int64_t ir = ((int64_t)r[2] * g.n[1] + r[1]) * g.n[0] + r[0];
-        T pr[5];
-        primitives<T>(q, N, ir, cf.inv_cv, cf.form, pr);
-        v[mi][0] = pr[1];
-        v[mi][1] = pr[2];
-        v[mi][2] = pr[3];
-        v[mi][3] = pr[4];
+      for (int c = 0; c < kNQ; ++c) {
+        const double qv = (double)v[c];
+        s[c] += qv;
+        if (!isfinite(qv)) nonfin = 1;
       }
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const T num = M == 2 ? (v[0][c] - T(8) * v[1][c] + T(8) * v[2][c] - v[3][c])
-                             : (T(9) * v[1][c] - v[0][c]) + T(45) * (v[3][c] - v[2][c]) + (v[5][c] - T(9) * v[4][c]);
-        G[c < 3 ? 3 * c + d : 9 + d] = num * (M == 2 ? cf.inv12h[d] : cf.inv60h[d]);
-      }
+      s[5] += 0.5 * (double)pr[0] * uu;
+      s[8] += uu;
+      s[9] += (double)pr[4];
+      s[10] = fmax(s[10], uu);
+      if (nonfin) s[11] = 1.0;
     }
-    T pr[5];
-    primitives<T>(q, N, i, cf.inv_cv, cf.form, pr);
-    const double tt = (double)pr[4] * (double)cf.inv_tref;
-    const double mu = cf.visc == 1 ? (double)cf.mu_ref * tt * sqrt(tt) * (1.0 / (double)cf.inv_tref + (double)cf.suth_s) /
-                                         ((double)pr[4] + (double)cf.suth_s)
-                                   : (double)cf.mu_ref * pow(tt, (double)cf.mu_exp);
-    const double th = (double)G[0] + (double)G[4] + (double)G[8];
-    double eps = 0.0;
+  };
 #pragma unroll
-    for (int ii = 0; ii < 3; ++ii)
+  for (int j = 0; j < 2 * M; ++j) {
+    const int z = z0 - M + j;
+    T v[5], pr[5];
+    fetch(col, z, v);
+    absorb(v, act && j >= M && z < z1, pr);
 #pragma unroll
-      for (int jj = 0; jj < 3; ++jj) {
-        double sg = mu * ((double)G[3 * ii + jj] + (double)G[3 * jj + ii]);
-        if (ii == jj) sg -= (2.0 / 3.0) * mu * th;
-        eps += sg * (double)G[3 * ii + jj];
-      }
-    const double ox = (double)G[7] - (double)G[5];
-    const double oy = (double)G[2] - (double)G[6];
-    const double oz = (double)G[3] - (double)G[1];
-    const double u = pr[1], v = pr[2], w = pr[3];
-    const double uu = u * u + v * v + w * w;
-    int nonfin = 0;
-#pragma unroll
-    for (int c = 0; c < kNQ; ++c) {
-      const double qv = (double)q[c * N + i];
-      s[c] = qv;
-      if (!isfinite(qv)) nonfin = 1;
-    }
-    s[5] = 0.5 * (double)pr[0] * uu;
-    s[6] = eps;
-    s[7] = ox * ox + oy * oy + oz * oz;
-    s[8] = uu;
-    s[9] = (double)pr[4];
-    s[10] = sqrt(uu);
-    s[11] = nonfin;
+    for (int c = 0; c < 3; ++c) win[c][j] = pr[1 + c];
+    if (j >= M) tw[j - M] = pr[4];
   }
-  __shared__ double red[4][kNStat];
-  const int lane = threadIdx.x, wave = threadIdx.y;
+  T nq[5], hq[5];
+  fetch(col, z0 + M, nq);
+  fetch(hcol, z0, hq);
+  for (int z = z0; z < z1; ++z) {
+    T* sp = &s_u[(z - z0) & 1][0][0][0];
+    {
+      T pr[5];
+      absorb(nq, act && z + M < z1, pr);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) win[c][2 * M] = pr[1 + c];
+      tw[M] = pr[4];
+    }
+    if (act) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sp[(c * LH + ty + M) * LW + tx + M] = win[c][M];
+    }
+    if (hl >= 0) {
+      T pr[5];
+      absorb(hq, false, pr);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sp[c * LH * LW + hl] = pr[1 + c];
+    }
+    if (z + 1 < z1) {
+      fetch(col, z + 1 + M, nq);
+      fetch(hcol, z + 1, hq);
+    }
+    __syncthreads();
+    if (act) {
+      T G[9];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const T* p = sp + (c * LH + ty + M) * LW + tx + M;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          T v[2 * M];
+#pragma unroll
+          for (int mi = 0; mi < 2 * M; ++mi) {
+            const int m = mi < M ? mi - M : mi - M + 1;
+            v[mi] = d == 0 ? p[m] : (d == 1 ? p[m * LW] : win[c][M + m]);
+          }
+          const T num = M == 2 ? (v[0] - T(8) * v[1] + T(8) * v[2] - v[3])
+                               : (T(9) * v[1] - v[0]) + T(45) * (v[3] - v[2]) + (v[5] - T(9) * v[4]);
+          G[3 * c + d] = num * (M == 2 ? cf.inv12h[d] : cf.inv60h[d]);
+        }
+      }
+      const double temp = (double)tw[0], tt = temp * (double)cf.inv_tref;
+      const double mu = cf.visc == 1 ? (double)cf.mu_ref * tt * sqrt(tt) * (1.0 / (double)cf.inv_tref + (double)cf.suth_s) /
+                                           (temp + (double)cf.suth_s)
+                                     : (double)cf.mu_ref * pow(tt, (double)cf.mu_exp);
+      const double th = (double)G[0] + (double)G[4] + (double)G[8];
+      double eps = 0.0;
+#pragma unroll
+      for (int ii = 0; ii < 3; ++ii)
+#pragma unroll
+        for (int jj = 0; jj < 3; ++jj) {
+          double sg = mu * ((double)G[3 * ii + jj] + (double)G[3 * jj + ii]);
+          if (ii == jj) sg -= (2.0 / 3.0) * mu * th;
+          eps += sg * (double)G[3 * ii + jj];
+        }
+      const double ox = (double)G[7] - (double)G[5];
+      const double oy = (double)G[2] - (double)G[6];
+      const double oz = (double)G[3] - (double)G[1];
+      s[6] += eps;
+      s[7] += ox * ox + oy * oy + oz * oz;
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+      for (int j = 0; j < 2 * M; ++j) win[c][j] = win[c][j + 1];
+#pragma unroll
+    for (int j = 0; j < M; ++j) tw[j] = tw[j + 1];
+  }
+  s[10] = sqrt(s[10]);
 #pragma unroll
   for (int c = 0; c < kNStat; ++c) {
     double v = s[c];
@@ -124,73 +194,80 @@ __global__ __launch_bounds__(256) void k_stats(Geom g, Coef<T> cf, const T* __re
     } else {
       v = wave_sum(v);
     }
-    if (lane == 0) red[wave][c] = v;
+    if (tx == 0) red[ty][c] = v;
   }
   __syncthreads();
-  if (wave == 0 && lane < kNStat) {
-    double v;
-    if (lane == 10 || lane == 11)
-      v = fmax(fmax(red[0][lane], red[1][lane]), fmax(red[2][lane], red[3][lane]));
-    else
-      v = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
-    const int64_t blk = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    part[blk * kNStat + lane] = v;
+  if (tid < kNStat) {
+    double v = red[0][tid];
+    for (int r = 1; r < kSY; ++r) v = tid == 10 || tid == 11 ? fmax(v, red[r][tid]) : v + red[r][tid];
+    part[(int64_t)blk * kNStat + tid] = v;
   }
 }
 
-// Fixed-order final reduction: out[0..12] statistics, out[13..17] RK totals partial sums.
+// Planes of a workgroup of k_stats, and its workgroups: 64 planes, or as many fewer as leave 1024
+// workgroups (a march reads 2 M planes more than it owns).
+int stats_zc(const Geom& g) {
+  const int64_t tiles = (int64_t)((g.n[0] + kSX - 1) / kSX) * ((g.n[1] + kSY - 1) / kSY);
+  return (int)std::max<int64_t>(4, std::min<int64_t>(64, tiles * g.n[2] / 1024));
+}
+int64_t stats_workgroups(const Geom& g) {
+  const int zc = stats_zc(g);
+  return (int64_t)((g.n[0] + kSX - 1) / kSX) * ((g.n[1] + kSY - 1) / kSY) * ((g.n[2] + zc - 1) / zc);
+}
+
 // Fixed-order two-level reduction of the per-block partials (deterministic: the order depends only
 // on the partial counts).  Level 1: workgroup j reduces its contiguous share of the statistic
 // partials [nblk][13] and of the FP64 RK-total slots [ntot][5] into mid[j][18]; level 2 reduces
 // the kStatRed rows of mid into out[18].  Components 10 (max |u|) and 11 (non-finite flag) take
-// the maximum, the others the sum.
+// the maximum, the others the sum.  A wave takes a component: its lanes stride over the entries and
+// are added by lane exchanges (a tree of 8 barriers for each of the 18 components took 17 us a level).
 constexpr int kStatOut = kNStat + kNQ;
-static_assert(kStatRed == 256, "level 2 gives one thread per level-1 row");
+static_assert(kStatRed == 256, "level 2 gives four level-1 rows to a lane");
 
-__device__ __forceinline__ double tree256(double* red, double v, bool is_max) {
-  const int t = threadIdx.x;
-  red[t] = v;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (t < s) red[t] = is_max ? fmax(red[t], red[t + s]) : red[t] + red[t + s];
-    __syncthreads();
+__device__ __forceinline__ double wave_reduce(double v, bool is_max) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(v, off, 64);
+    v = is_max ? fmax(v, o) : v + o;
   }
-  const double r = red[0];
-  __syncthreads();
-  return r;
+  return v;
 }
 
 __global__ __launch_bounds__(256) void k_stats_reduce(const double* __restrict__ part, int64_t nblk,
                                                       const double* __restrict__ tot_part, int64_t ntot,
                                                       double* __restrict__ mid) {
-  __shared__ double red[256];
-  const int t = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t j = blockIdx.x;
   const int64_t lp = (nblk + kStatRed - 1) / kStatRed, lt = (ntot + kStatRed - 1) / kStatRed;
   const int64_t p0 = j * lp, p1 = min(p0 + lp, nblk), t0 = j * lt, t1 = min(t0 + lt, ntot);
-  for (int c = 0; c < kStatOut; ++c) {
+  for (int c = wave; c < kStatOut; c += 4) {
     const bool is_max = (c == 10 || c == 11);
     double v = 0.0;
     if (c < kNStat) {
-      for (int64_t b = p0 + t; b < p1; b += 256) {
+      for (int64_t b = p0 + lane; b < p1; b += 64) {
         const double pv = part[b * kNStat + c];
         v = is_max ? fmax(v, pv) : v + pv;
       }
     } else if (tot_part) {
-      for (int64_t b = t0 + t; b < t1; b += 256) v += tot_part[b * kNQ + (c - kNStat)];
+      for (int64_t b = t0 + lane; b < t1; b += 64) v += tot_part[b * kNQ + (c - kNStat)];
     }
-    const double r = tree256(red, v, is_max);
-    if (t == 0) mid[j * kStatOut + c] = r;
+    v = wave_reduce(v, is_max);
+    if (lane == 0) mid[j * kStatOut + c] = v;
   }
 }
 
-__global__ __launch_bounds__(256) void k_stats_final(const double* __restrict__ mid, double* __restrict__ out) {
-  __shared__ double red[256];
-  const int t = threadIdx.x;
-  for (int c = 0; c < kStatOut; ++c) {
+__global__ __launch_bounds__(1024) void k_stats_final(const double* __restrict__ mid, double* __restrict__ out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int c = wave; c < kStatOut; c += 16) {
     const bool is_max = (c == 10 || c == 11);
-    const double r = tree256(red, t < kStatRed ? mid[t * kStatOut + c] : 0.0, is_max);
-    if (t == 0) out[c] = r;
+    double v = mid[lane * kStatOut + c];
+#pragma unroll
+    for (int r = 1; r < kStatRed / 64; ++r) {
+      const double o = mid[(r * 64 + lane) * kStatOut + c];
+      v = is_max ? fmax(v, o) : v + o;
+    }
+    v = wave_reduce(v, is_max);
+    if (lane == 0) out[c] = v;
   }
 }
 
@@ -299,16 +376,17 @@ hipError_t launch_stats(const Geom& g, const Coef<T>& cf, const T* q, double* pa
                         const double* tot_part, int64_t ntot_blocks, double gamma, hipStream_t stream,
                         LaunchHook* hook) {
   (void)gamma;
-  const dim3 blk(kBX, kBY, 1);
-  const dim3 gr = grid_of(g);
+  const dim3 blk(kSX, kSY, 1);
+  const int64_t nblk = stats_workgroups(g);  // at most stats_blocks(g), the partials there is room for
+  const int zc = stats_zc(g);
   if (g.order == 6)
-    HOOKED(kKStats, hipLaunchKernelGGL((k_stats<T, 3>), gr, blk, 0, stream, g, cf, q, part));
+    HOOKED(kKStats, hipLaunchKernelGGL((k_stats<T, 3>), dim3((unsigned)nblk), blk, 0, stream, g, cf, q, part, zc));
   else
-    HOOKED(kKStats, hipLaunchKernelGGL((k_stats<T, 2>), gr, blk, 0, stream, g, cf, q, part));
+    HOOKED(kKStats, hipLaunchKernelGGL((k_stats<T, 2>), dim3((unsigned)nblk), blk, 0, stream, g, cf, q, part, zc));
   double* mid = out + kStatOutSlots;
-  hipLaunchKernelGGL(k_stats_reduce, dim3(kStatRed), dim3(256), 0, stream, part, stats_blocks(g), tot_part,
+  hipLaunchKernelGGL(k_stats_reduce, dim3(kStatRed), dim3(256), 0, stream, part, nblk, tot_part,
                      ntot_blocks, mid);
-  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, stream, (const double*)mid, out);
+  hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(1024), 0, stream, (const double*)mid, out);
   return hipGetLastError();
 }
 
