@@ -88,3 +88,20 @@ def test_paper_form_tiles(n, p):
 
 def test_paper_form_tiles_fp32():
     check((34, 30, 36), (2, 2, 3), form=1, precision="fp32", tol=2e-6)
+
+
+@pytest.mark.parametrize("n,prec", [((1024, 8, 16), "fp64"), ((8, 1024, 32), "fp64"), ((64, 16, 1024), "fp64"),
+                                    ((256, 128, 8), "fp32"), ((16, 256, 128), "fp64"), ((8, 8, 512), "fp32"),
+                                    ((32, 512, 8), "fp64")])
+def test_diagnostics_line_lengths(n, prec):
+    """Every length of a transformed line (one to four stages, the last of radix 8, 4 or 2) in x, y and
+    z, fewer columns than a tile and shells beyond the last; bars as in test_gpu_diag.py."""
+    from oracle.diagnostics import diagnostics as oracle_diagnostics
+    from tests.test_gpu_diag import cfg_pair, check
+    q = smooth_levels(n, 1, 3, 0)[0]
+    q[:, ::3] *= 1.01  # (energy beyond the lowest shells)
+    dq = torch.from_numpy(q).to("cuda", torch.float32 if prec == "fp32" else torch.float64).contiguous()
+    nshell, nb = max(n) // 3, 20
+    gc, oc = cfg_pair(n, 4 if n[0] > 16 else 6, prec)
+    got = atns.field_diagnostics(gc, dq.data_ptr(), nshell, nb, 6.0, 6.0)
+    check(got, oracle_diagnostics(oc, dq.double().cpu().numpy(), nshell, nb, 6.0, 6.0), nb, 6.0, 6.0, f"{n} {prec}")
