@@ -123,6 +123,13 @@ constexpr ShapeCost kShapeCost[2][3][kShapes] = {
      {{5, 3.0, 4.8}, {1, 6.0, 13.0}, {6, 6.0, 13.0}, {3, 5.6, 8.6}}}};
 constexpr int kComputeUnits = 256;
 
+namespace {
+double march_cost(const ShapeCost& c, int64_t workgroups, int zc) {
+  const double rounds = (double)((workgroups + kComputeUnits - 1) / kComputeUnits);
+  return (zc + 4) * std::sqrt(std::sqrt(std::pow(c.alone, 4) + std::pow(rounds * c.busy, 4)));
+}
+}  // namespace
+
 // Small grids are cut into short z chunks so that they reach every compute unit (32^3 in FP64 ran on
 // 4 of them, 300 us a delayed stage; now 40), large ones into long ones (fewer planes twice).
 void default_shape(const Geom& g, int precision, bool forced, bool at, int* tile, int* zchunk) {
@@ -137,8 +144,7 @@ void default_shape(const Geom& g, int precision, bool forced, bool at, int* tile
     int zbest = g.n[2];
     for (int nc = 1; nc <= g.n[2] / 4; nc += nc < 16 ? 1 : nc / 8) {
       const int zc = (g.n[2] + nc - 1) / nc;
-      const double rounds = (double)((fused_blocks(g, t, zc) + kComputeUnits - 1) / kComputeUnits);
-      const double cost = (zc + 4) * std::sqrt(std::sqrt(std::pow(c->alone, 4) + std::pow(rounds * c->busy, 4)));
+      const double cost = march_cost(*c, fused_blocks(g, t, zc), zc);
       if (cost < best) {
         best = cost;
         zbest = zc;
@@ -150,6 +156,29 @@ void default_shape(const Geom& g, int precision, bool forced, bool at, int* tile
       *zchunk = std::max(4, zbest);
     }
   }
+}
+
+// The z chunk of runs of n[0 .. m)^3 points advanced together with `tile`, by the same cost: every
+// workgroup of a launch is counted, and all march at most zc planes.
+int batch_zchunk(const int* n, int m, int precision, int tile) {
+  const ShapeCost* c = kShapeCost[precision == AT_FP32 ? 0 : 1][1];
+  int nmax = 4, row = 0;
+  for (int i = 0; i < m; ++i) nmax = std::max(nmax, n[i]);
+  while (row < kShapes && c[row].tile != tile) ++row;
+  if (row == kShapes) return 64;
+  double best = 1e300;
+  int zbest = nmax;
+  for (int nc = 1; nc <= nmax / 4; nc += nc < 16 ? 1 : nc / 8) {
+    const int zc = (nmax + nc - 1) / nc, bx = tile_bx(tile), by = tile_by(tile);
+    int64_t workgroups = 0;
+    for (int i = 0; i < m; ++i) workgroups += (int64_t)((n[i] + bx - 1) / bx) * ((n[i] + by - 1) / by) * ((n[i] + zc - 1) / zc);
+    const double cost = march_cost(c[row], workgroups, zc);
+    if (cost < best) {
+      best = cost;
+      zbest = zc;
+    }
+  }
+  return zbest;
 }
 
 }  // namespace atns

@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <chrono>
 #include <deque>
+#include <functional>
 #include <new>
 #include <string>
 #include <thread>
@@ -191,10 +192,21 @@ extern "C" int at_serve(const at_serve_config* sc, const at_request* reqs, int32
     rc = sc->tile_delayed >= 0
              ? at_batch_set_stage_tuning(batch, sc->tile, sc->zchunk, sc->tile_delayed, sc->zchunk_delayed)
              : at_batch_set_tuning(batch, sc->tile, sc->zchunk);
-    if (rc) {
-      at_batch_destroy(batch);
-      return rc;
-    }
+  } else if (nreq > 0) {
+    // the batch's tile, and the z chunk that suits the trace's largest runs when every slot is taken
+    // (from the trace alone, so that the totals' summation order does not follow the arrival times):
+    // 12 runs of 32^3 .. 96^3 are 368 workgroups with z chunks of 64 and 1008 with the 20 chosen
+    // here, 65.8 -> 54.7 ms
+    std::vector<int> n((size_t)nreq);
+    for (int i = 0; i < nreq; ++i) n[(size_t)i] = reqs[i].n;
+    std::sort(n.begin(), n.end(), std::greater<int>());
+    int tile = 0, zc = 0;
+    rc = at_batch_get_tuning(batch, &tile, &zc);
+    if (!rc) rc = at_batch_set_tuning(batch, tile, batch_zchunk(n.data(), std::min(nreq, sc->max_active), sc->precision, tile));
+  }
+  if (rc) {
+    at_batch_destroy(batch);
+    return rc;
   }
   hipStream_t prep = nullptr;
   if (hipStreamCreateWithFlags(&prep, hipStreamNonBlocking) != hipSuccess) {

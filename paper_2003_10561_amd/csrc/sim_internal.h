@@ -84,6 +84,9 @@ Geom make_geom(const at_config* c);
 // those that do, by the cost model in atns_host.hip.
 void default_shape(const Geom& g, int precision, bool forced, bool at, int* tile, int* zchunk);
 
+// Default z chunk of runs of n[0 .. m)^3 points that advance together with this tile.
+int batch_zchunk(const int* n, int m, int precision, int tile);
+
 // Removes a run from its batch (called when the run is destroyed).
 void batch_forget(at_batch* b, at_sim* s);
 

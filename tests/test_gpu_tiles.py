@@ -105,3 +105,24 @@ def test_diagnostics_line_lengths(n, prec):
     gc, oc = cfg_pair(n, 4 if n[0] > 16 else 6, prec)
     got = atns.field_diagnostics(gc, dq.data_ptr(), nshell, nb, 6.0, 6.0)
     check(got, oracle_diagnostics(oc, dq.double().cpu().numpy(), nshell, nb, 6.0, 6.0), nb, 6.0, 6.0, f"{n} {prec}")
+
+
+@pytest.mark.parametrize("prec,shape", [("fp32", (1, 64)), ("fp64", (5, 64))])
+def test_serve_default_shape(prec, shape):
+    """The z chunk that the server derives from the trace never changes a field: every final state of
+    a mixed burst equals that of one long chunk, bit for bit."""
+    reqs = []
+    for i, (n, p) in enumerate(((16, 2), (48, 3), (32, 2), (64, 2), (40, 4), (16, 1))):
+        q = smooth_levels((n,) * 3, 1, 40 + i, 0)[0]
+        reqs.append(dict(arrival_s=0.0, n=n, p=p, steps=5 + i, mode=(atns.CAA, atns.SAA, atns.SYNC)[i % 3], L=1 + i % 2,
+                         seed=i, dt=0.2 * 2 * np.pi / n / 2.0, mu_ref=0.01, q0=q, q_final=np.empty_like(q)))
+    for r in reqs:
+        r["L"] = 0 if r["mode"] == atns.SYNC else r["L"]
+    got = {}
+    for k in ("default", "long"):
+        kw = {} if k == "default" else dict(tile=shape[0], zchunk=shape[1])
+        res, _ = atns.serve(reqs, precision=prec, max_active=4, **kw)
+        assert [o["status"] for o in res] == [0] * len(reqs)
+        got[k] = [r["q_final"].copy() for r in reqs]
+    for i, (a, b) in enumerate(zip(got["default"], got["long"])):
+        assert np.isfinite(a).all() and np.array_equal(a, b), i
