@@ -119,8 +119,8 @@ constexpr ShapeCost kShapeCost[2][3][kShapes] = {
      {{1, 3.0, 2.35}, {0, 2.8, 4.0}, {5, 2.7, 1.35}, {6, 3.2, 3.8}},
      {{1, 3.2, 3.1}, {5, 3.0, 2.4}, {6, 3.4, 3.3}, {0, 5.0, 7.3}}},
     {{{1, 2.5, 3.65}, {5, 2.95, 2.09}, {6, 2.6, 3.7}, {3, 3.0, 3.3}},
-     {{5, 3.0, 4.36}, {1, 6.0, 9.7}, {6, 6.0, 8.9}, {3, 5.6, 8.4}},
-     {{5, 3.0, 4.8}, {1, 6.0, 13.0}, {6, 6.0, 13.0}, {3, 5.6, 8.6}}}};
+     {{5, 3.0, 4.36}, {1, 5.0, 6.5}, {6, 5.0, 6.5}, {3, 5.6, 8.4}},
+     {{5, 3.0, 4.8}, {1, 8.0, 11.4}, {6, 8.0, 11.4}, {3, 5.6, 8.6}}}};
 constexpr int kComputeUnits = 256;
 
 namespace {

@@ -180,7 +180,8 @@ __device__ __forceinline__ T own_copy(T v) {
   return r;
 }
 
-// Primitives from conserved values: rho, u, v, w, T.
+// Primitives from conserved values: rho, u, v, w, T (in one association in every instantiation, so
+// that a point's T does not depend on which of them, or which part of a march, forms it).
 template <typename T>
 __device__ __forceinline__ void prim_of(const T q[5], T inv_cv, T& r, T& u, T& v, T& w, T& t) {
   r = q[0];
@@ -188,7 +189,7 @@ __device__ __forceinline__ void prim_of(const T q[5], T inv_cv, T& r, T& u, T& v
   u = q[1] * ri;
   v = q[2] * ri;
   w = q[3] * ri;
-  t = (q[4] * ri - T(0.5) * (u * u + v * v + w * w)) * inv_cv;
+  t = fmaT(ri, q[4], T(-0.5) * fmaT(w, w, fmaT(u, u, v * v))) * inv_cv;
 }
 
 // Thread roles of a workgroup (one column of the z march each, wave-uniform):
@@ -291,6 +292,13 @@ template <typename T, int BX, int BY, bool PUB, bool AT, bool SUB, bool AB2 = fa
 __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, const int bkx, const int bky,
                                            const int bkz, const uint32_t blk) {
   constexpr bool kMask = AT && !SUB, kSub = AT && SUB;
+  // kBlock (FP64 with AT): the masked derivatives in blocks of their own, not formed beside the central
+  // ones and selected, which costs every wave 64 instructions a plane; and the threads without a column
+  // push what they fetched into their windows too (nobody reads it), because a branch copies the
+  // window where its paths meet.  256^3 delayed stage, 32 x 8 tiles: 2733 -> 2100 us with the first,
+  // 1870 with both.  Elsewhere the registers spill or the autotuned step gains nothing: FP64 without AT
+  // 957 -> 1104 us with the push, FP32 with AT 539 -> 595 us with both, 512^3 FP32 no change.
+  constexpr bool kBlock = AT && sizeof(T) == 8;
   using TL = Tile<BX, BY>;
   constexpr int LW = TL::LW, LH = TL::LH;
   __shared__ T s_pr[2][4][LH][LW];       // u, v, w, T of a plane (two buffers: planes alternate)
@@ -426,6 +434,10 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
 
   // (zero where a lane never fetches them: every path then reads defined values, see below)
   T raw[5], xraw[5] = {}, fq[5] = {}, fd[5] = {};
+  if (kBlock) {
+#pragma unroll
+    for (int c = 0; c < 5; ++c) raw[c] = T(0);
+  }
   T acc[5][kNQ];
   if (role == 0) {
 #pragma unroll
@@ -640,7 +652,7 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
         sx[c] = kMask ? vx[c] : T(0);
         sy[c] = kMask ? vy[c] : T(0);
       }
-      if (kSub && wx && kcx > 0) {
+      if (kSub && !kBlock && wx && kcx > 0) {
         // a halo column next to its own delayed x face: its AT sums, formed a plane ahead, or from
         // the two extrapolated values at its face's reader slots
         if (kHv) {
@@ -654,7 +666,7 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
                                                             a.gv[o + 1 + (uint32_t)c * a.slab0]);
         }
       }
-      if (kSub && wy && kcy > 0) {
+      if (kSub && !kBlock && wy && kcy > 0) {
         const uint32_t o = (uint32_t)gz * zsy + opy - (uint32_t)(lye < 2 ? lye : lye - a.ey + 2) * (uint32_t)nx;
         const bool lo = lye < 2, outer = lye == 0 || lye == a.ey - 1;
 #pragma unroll
@@ -669,11 +681,54 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
                 yp2 = s_pr[bc][c][py + 2][px];
         T dx = central_num(xm2, xm1, xp1, xp2);
         T dy = central_num(ym2, ym1, yp1, yp2);
-        if (wx && kcx > 0) dx = masked_num(xm2, xm1, xp1, xp2, cxm, sx[c]);
-        if (wy && kcy > 0) dy = masked_num(ym2, ym1, yp1, yp2, cym, sy[c]);
+        if (!kBlock && wx && kcx > 0) dx = masked_num(xm2, xm1, xp1, xp2, cxm, sx[c]);
+        if (!kBlock && wy && kcy > 0) dy = masked_num(ym2, ym1, yp1, yp2, cym, sy[c]);
         set_grad(G, c, 0, dx * a.i12x);
         set_grad(G, c, 1, dy * a.i12y);
         set_grad(G, c, 2, (WIN(c, 0) - T(8) * WIN(c, 1) + T(8) * WIN(c, 3) - WIN(c, 4)) * a.i12z);
+      }
+      // (the sums once more, written out: as a function shared with the above they move FP32's register
+      // allocation, 1% of its SUB stages)
+      if (kBlock && wx) {
+        if (kSub && kcx > 0) {
+        // a halo column next to its own delayed x face: its AT sums, formed a plane ahead, or from
+        // the two extrapolated values at its face's reader slots
+        if (kHv) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c) sx[c] = s_hv[c][hslot];
+        } else {
+          const uint32_t o = (uint32_t)gz * zsx + opx - (uint32_t)(lxe < 2 ? lxe : lxe - a.ex + 2);
+          const bool lo = lxe < 2, outer = lxe == 0 || lxe == a.ex - 1;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) sx[c] = at_sum_of<T>(lo, outer, a.gv[o + (uint32_t)c * a.slab0],
+                                                            a.gv[o + 1 + (uint32_t)c * a.slab0]);
+        }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(sx[c]));  // (keeps the block a block)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const T m2 = s_pr[bc][c][py][px - 2], m1 = s_pr[bc][c][py][px - 1], p1 = s_pr[bc][c][py][px + 1],
+                  p2 = s_pr[bc][c][py][px + 2];
+          if (kcx > 0) set_grad(G, c, 0, masked_num(m2, m1, p1, p2, cxm, sx[c]) * a.i12x);
+        }
+      }
+      if (kBlock && wy) {
+        if (kSub && kcy > 0) {
+        const uint32_t o = (uint32_t)gz * zsy + opy - (uint32_t)(lye < 2 ? lye : lye - a.ey + 2) * (uint32_t)nx;
+        const bool lo = lye < 2, outer = lye == 0 || lye == a.ey - 1;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sy[c] = at_sum_of<T>(lo, outer, a.gv[o + (uint32_t)c * a.slab1],
+                                                          a.gv[o + (uint32_t)nx + (uint32_t)c * a.slab1]);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(sy[c]));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const T m2 = s_pr[bc][c][py - 2][px], m1 = s_pr[bc][c][py - 1][px], p1 = s_pr[bc][c][py + 1][px],
+                  p2 = s_pr[bc][c][py + 2][px];
+          if (kcy > 0) set_grad(G, c, 1, masked_num(m2, m1, p1, p2, cym, sy[c]) * a.i12y);
+        }
       }
       if (__builtin_expect(kcz > 0, 0)) {
         // near a delayed z face (the same for the whole plane unless the column's PEs differ): the
@@ -926,7 +981,7 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
       }
 #pragma unroll
       for (int c = 0; c < 5; ++c) asm volatile("" ::"v"(xraw[c]));  // consumed on every path
-      if (column) {
+      if (kBlock || column) {
         T r_, u_, v_, w_, e_ = raw[4];
         prim_of<T>(raw, inv_cv, r_, u_, v_, w_, t_);
         if constexpr (sizeof(T) == 4) {
@@ -934,7 +989,7 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
           e_ = own_copy(e_);
         }
         zw.push(u_, v_, w_, t_, r_, e_);
-        if (!(kSub && gk > 0)) {  // (a ghost's entry is in place; its window keeps its own values)
+        if ((!kBlock || column) && !(kSub && gk > 0)) {  // (a ghost's entry is in place; its window keeps its own values)
           s_pr[bn][0][py][px] = zw.get(0, 2);
           s_pr[bn][1][py][px] = zw.get(1, 2);
           s_pr[bn][2][py][px] = zw.get(2, 2);
