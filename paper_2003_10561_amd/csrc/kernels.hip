@@ -37,7 +37,9 @@ __device__ __forceinline__ double wave_sum(double v) {
 // column tile through zc planes: each point's primitives are formed once (1.6 times with the halo; 13
 // times, a division each, when every point formed its neighbours' own), x and y neighbours come from
 // an LDS plane (two of them, one barrier a plane), z neighbours from a register window, and the loads
-// of the next plane are issued before the barrier.  256^3 FP64: 0.67 ms with a point per thread.
+// of the next plane are issued before the barrier.  Bound by FP64 arithmetic (a division and a power
+// per point).  256^3 FP64: 0.67 ms with a point per thread, 0.33 now; 32^3: 11 us and 17, but the
+// reductions' lane exchanges take the call from 69 to 47 us.
 constexpr int kSX = 64, kSY = 8;
 template <typename T, int M>
 __global__ __launch_bounds__(kSX* kSY) void k_stats(Geom g, Coef<T> cf, const T* __restrict__ q,
