@@ -189,7 +189,11 @@ __device__ __forceinline__ void prim_of(const T q[5], T inv_cv, T& r, T& u, T& v
   u = q[1] * ri;
   v = q[2] * ri;
   w = q[3] * ri;
-  t = fmaT(ri, q[4], T(-0.5) * fmaT(w, w, fmaT(u, u, v * v))) * inv_cv;
+  if constexpr (sizeof(T) == 8) {  // (FP32's contraction is this one everywhere)
+    t = fmaT(ri, q[4], T(-0.5) * fmaT(w, w, fmaT(u, u, v * v))) * inv_cv;
+  } else {
+    t = (q[4] * ri - T(0.5) * (u * u + v * v + w * w)) * inv_cv;
+  }
 }
 
 // Thread roles of a workgroup (one column of the z march each, wave-uniform):
