@@ -204,12 +204,21 @@ Layout make_layout(const at_config* c, const Geom& g) {
   // values (sixth order); the flux buffer (sixth order)
   L.gv = take(c->form == 0 ? (size_t)3 * g.ring_slot * w : 0);
   L.flux = take(c->order == 6 ? (size_t)3 * kNQ * N * w : 0);
-  L.grad = take(c->form == 1 ? (size_t)kNGrad * N * w : 0);
-  // smallest tile (16 x 4) and smallest z chunk (4) bound the workgroup count of any stage launch
-  L.ntot = (int64_t)((c->n[0] + 15) / 16) * ((c->n[1] + 3) / 4) * ((c->n[2] + 3) / 4);
-  if (c->order == 6) L.ntot = std::max<int64_t>(L.ntot, blocks6(g));
-  if (c->form == 1) L.ntot = std::max<int64_t>(L.ntot, paper_blocks(g));
-  L.tot_part = take((size_t)L.ntot * kNQ * 8);
+  if (c->form == 1) {
+    // Form 1 stores nine gradients in a region of kNGrad, and keeps the slots of its FP64 totals behind
+    // them: 40 bytes a workgroup against the 12 N bytes left over in FP32 and at least 12 points a
+    // workgroup (grids of few columns, cut into bricks of one plane).  The bytes a caller has to bring
+    // therefore do not follow how finely the kernels cut a grid.
+    L.ntot = paper_blocks(g);
+    const size_t nine = align_up((size_t)9 * N * w);
+    L.grad = take(std::max((size_t)kNGrad * N * w, nine + (size_t)L.ntot * kNQ * 8));
+    L.tot_part = L.grad + nine;
+  } else {
+    // smallest tile (16 x 4) and smallest z chunk (4) bound the workgroup count of any stage launch
+    L.ntot = (int64_t)((c->n[0] + 15) / 16) * ((c->n[1] + 3) / 4) * ((c->n[2] + 3) / 4);
+    if (c->order == 6) L.ntot = std::max<int64_t>(L.ntot, blocks6(g));
+    L.tot_part = take((size_t)L.ntot * kNQ * 8);
+  }
   L.stat_part = take((size_t)stats_blocks(g) * kNStat * 8);
   L.stat_out = take(kStatOutBytes);
   L.force_table = take((size_t)kMaxPairs * c->n[0] * 6 * w);

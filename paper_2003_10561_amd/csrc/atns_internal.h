@@ -156,7 +156,7 @@ struct StagePArgs {
   T* q;
   T* q_out;
   T* dq;
-  T* grad;            // [9][N] (of a buffer of 12)
+  T* grad;            // [9][N] (the totals of tot_part lie behind them)
   T* ring;            // R slots of 5 * sum_d slab[d]
   T* rhs_out;
   const int8_t* delays;

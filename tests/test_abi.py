@@ -83,6 +83,16 @@ def test_workspace_bytes_formula_paper_form(lib):
     assert atns.workspace_bytes(cfg(form=1, visc_law=1, sutherland_s=0.4)) == b64
 
 
+@pytest.mark.parametrize("n,p,precision,allotted", [
+    ((141, 100, 14), (3, 4, 1), "fp64", 68098048), ((11, 132, 124), (1, 4, 4), "fp64", 65947648),
+    ((45, 128, 40), (1, 1, 1), "fp32", 31203840), ((10, 10, 100), (2, 2, 20), "fp32", 4039424),
+    ((5, 5, 5), (1, 1, 1), "fp32", 91392), ((256, 256, 256), (4, 4, 4), "fp32", 2199025920)])
+def test_paper_form_fits_allotted_workspaces(lib, n, p, precision, allotted):
+    """A workspace of 16-plane bricks' totals (the sizes that callers of the paper's form have allotted)
+    stays large enough however finely its kernels cut small and ragged grids."""
+    assert 0 < atns.workspace_bytes(cfg(n=n, p=p, form=1, precision=precision)) <= allotted
+
+
 @pytest.mark.parametrize("bad", [dict(n=(30, 32, 32), p=(4, 2, 1)), dict(p=(16, 2, 1)), dict(order=8),
                                  dict(order=6, p=(8, 2, 1)), dict(order=6, forcing=True),
                                  dict(form=2), dict(visc_law=1, sutherland_s=0.4), dict(form=1, visc_law=1),
