@@ -215,6 +215,38 @@ def test_autotune_keeps_state_and_uses_cache(tmp_path):
     assert cache.read_text().count("\n") == 1
 
 
+@pytest.mark.parametrize("n,p,precision", [((32, 32, 32), (2, 2, 2), "fp64"), ((60, 80, 100), (2, 2, 2), "fp64"),
+                                           ((48, 48, 48), (3, 3, 3), "fp32")])
+def test_autotune_of_a_lone_run_keeps_up_with_its_default(n, p, precision):
+    """Small grids take short z chunks by default; the tuned shapes of such a run step no slower.  The
+    bar lies half way between equal and the 1.4 times of a tuner that cannot choose those chunks."""
+    q = smooth_state(n, 55)
+    s = atns.Sim(atns.Config(n=n, p=p, dt=1e-3, mu_ref=0.01, max_delay=3, precision=precision))
+    s.init_field(q)
+    s.set_delay_schedule(atns.CAA, L=3, c_r=4, n_steps=600)
+    default = s.get_stage_tuning()
+    b = atns.Batch(precision)
+    b.add(s)
+    b.autotune(None, reps=20)
+    tuned = b.get_stage_tuning()
+    b.remove(s)
+    b.close()
+    us = {default: 1e9, tuned: 1e9}
+    e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for _ in range(4):
+        for shape in us:
+            s.set_stage_tuning(*shape)
+            s.rk_step(4)
+            e0.record()
+            s.rk_step(32)
+            e1.record()
+            e1.synchronize()
+            us[shape] = min(us[shape], e0.elapsed_time(e1) / 32 * 1e3)
+    say(f"case autotuned {n} {precision}: default {default} {us[default]:.1f} us, tuned {tuned} {us[tuned]:.1f} us")
+    assert us[tuned] <= 1.2 * us[default]
+    s.close()
+
+
 def test_autotune_keeps_adams_bashforth_register():
     """Adams-Bashforth steps keep dt f^{n-1} in the RK register (Sec. 2.2, Eq. time_ab).  Autotuning
     a batch that holds such a run (trial stages between steps) must leave that register alone, so
