@@ -126,3 +126,80 @@ def test_serve_default_shape(prec, shape):
         got[k] = [r["q_final"].copy() for r in reqs]
     for i, (a, b) in enumerate(zip(got["default"], got["long"])):
         assert np.isfinite(a).all() and np.array_equal(a, b), i
+
+
+# FP32 marches with two alternating flux planes and one barrier a plane, FP64 with one plane: edges 6 and
+# 6 x 7 (two halo points a thread), 21 x 25 (rows of 9 + 9 + 7, z chunks of 9 + 9 + 9 + 6), 65 x 9 (columns
+# of 22 + 22 + 21), 37 x 19 (19 + 18 by 10 + 9), 59 x 13 (30 + 29 by 7 + 6, two halo points a thread).
+# FP32 bar as in test_gpu_order6.py (a ghost value carries the rounding of its terms, 6e-8, times at most
+# 200, and enters a field through dt / h < 0.05: 6e-7)
+@pytest.mark.parametrize("n,p", [((6, 6, 6), (1, 1, 1)), ((12, 14, 40), (2, 2, 1)), ((42, 25, 33), (2, 1, 1)),
+                                 ((130, 9, 12), (2, 1, 1)), ((37, 19, 18), (1, 1, 2)), ((59, 13, 17), (1, 1, 1))])
+@pytest.mark.parametrize("precision,tol", [("fp32", 2e-6), ("fp64", TOL64)])
+def test_order6_narrower_tiles(n, p, precision, tol):
+    check(n, p, order=6, precision=precision, tol=tol)
+
+
+# edges 30 x 25 (15 + 15 by 13 + 12), 17 x 15 (9 + 8 by 15), 15 x 17 (15 by 9 + 8)
+@pytest.mark.parametrize("n,p", [((60, 50, 20), (2, 2, 2)), ((34, 30, 20), (2, 2, 2)), ((30, 34, 18), (2, 2, 3))])
+@pytest.mark.parametrize("precision,tol", [("fp64", TOL64), ("fp32", 2e-6)])
+def test_paper_form_narrower_tiles(n, p, precision, tol):
+    check(n, p, form=1, precision=precision, tol=tol)
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", TOL64), ("fp32", 2e-6)])
+def test_paper_form_long_marches(precision, tol):
+    """256 tiles of 16 x 8 on 130 planes march 32 planes at a time (a smaller grid takes chunks of 8) over
+    z-PEs of 5: up to eight of them in a chunk, which starts inside one, with random delays on every
+    face of every one."""
+    check((256, 128, 130), (16, 16, 26), form=1, steps=1, precision=precision, tol=tol)
+
+
+@pytest.mark.parametrize("edge", [(10, 10, 10), (9, 11, 5)])
+def test_paper_form_ab2_on_small_pes(edge):
+    """Adams-Bashforth steps, then Runge-Kutta ones, then Adams-Bashforth again where a point takes a
+    thread (10 x 10 and 9 x 11 points fill less than half of a tile)."""
+    p = (2, 2, 2)
+    n = tuple(2 * e for e in edge)
+    q = smooth_levels(n, 6, 71, 1)
+    kw = dict(n=n, p=p, dt=2e-3, mu_ref=0.02, max_delay=3, form=1)
+    g, o = atns.Sim(atns.Config(precision="fp64", **kw)), Oracle(OracleConfig(**kw))
+    tab = np.random.default_rng(72).integers(0, 4, (14, 8, 6)).astype(np.int8)
+    g.init_field(q, 6)
+    o.init_field(q, 6)
+    tab[:5] = 0
+    g.set_delay_schedule(atns.EXPLICIT, table=tab)
+    o.set_schedule(atns.EXPLICIT, table=tab)
+    for s in (g, o):
+        s.ab2_step(3)
+        s.rk_step(2)
+        s.ab2_step(2)
+    a, b = g.get_field(), o.field()
+    err = max(float(np.linalg.norm(a[c] - b[c]) / np.linalg.norm(b[c])) for c in range(5))
+    print(f"case n={n} p={p} form=1 ab2: rel-L2 {err:.2e}", flush=True)
+    assert err <= TOL64
+    gs, os_ = g.stats(), o.stats()
+    for k in ("mass", "energy", "mass_rk", "energy_rk", "K", "eps", "enstrophy"):
+        assert abs(gs[k] - os_[k]) <= TOL64 * abs(os_[k]), (k, gs[k], os_[k])
+    g.close()
+
+
+@pytest.mark.parametrize("n,p", [((16, 16, 16), (1, 1, 1)), ((40, 24, 4), (1, 3, 1)), ((33, 20, 57), (1, 1, 3)),
+                                 ((72, 60, 40), (2, 2, 2)), ((64, 96, 80), (1, 3, 5)), ((8, 8, 200), (2, 2, 1))])
+def test_default_shapes(n, p):
+    """The shapes that a run takes by itself, for its synchronous and its delayed stages, against the
+    oracle in FP64, and against one long chunk of 32 x 8 tiles bit for bit in FP32."""
+    check(n, p)
+    q = smooth_levels(n, 4, 5, 0)
+    field = []
+    for shape in (None, (1, 64, 1, 64)):
+        s = atns.Sim(atns.Config(n=n, p=p, dt=2e-3, mu_ref=0.02, max_delay=1, precision="fp32"))
+        if shape:
+            s.set_stage_tuning(*shape)
+        print(f"case default shapes n={n} p={p} fp32: {s.get_stage_tuning()}", flush=True)
+        s.init_field(q, 4)
+        s.set_delay_schedule(atns.SAA, L=1, seed=9, n_steps=12)
+        s.rk_step(4)
+        field.append(s.get_field())
+        s.close()
+    assert np.isfinite(field[0]).all() and np.array_equal(field[0], field[1])
