@@ -100,15 +100,22 @@ Geom make_geom(const at_config* c) {
   return g;
 }
 
-// Cost of one plane of a workgroup's march in microseconds, measured on grids of 32^3 to 270 x 200 x
-// 150: `alone`, with the workgroup the only one of its compute unit (latency), and `busy`, per
-// workgroup with the compute unit full (throughput).  A workgroup of zc planes marches through
-// zc + 4, so a stage of n workgroups on 256 compute units takes about
-// (zc + 4) max(alone, ceil(n / 256) busy), rounded off where the two meet (their fourth powers are
-// added): within 10% of the times measured with 32 x 8 tiles on 32^3 (18.3 us with z chunks of 4, 43
-// with 16), 128^3 and 256^3.  Rows: FP32, FP64; per row stages
-// without AT stencils, with AT on tiles aligned with the PEs, with masked AT.  Tiles that won nowhere
-// are left out; the first of a row is taken unless another saves 5%.
+// Cost of one plane of a workgroup's march in microseconds: `alone`, with the workgroup the only one of
+// its compute unit (latency), and `busy`, per workgroup with the compute unit full (throughput).  A
+// workgroup of zc planes marches through zc + 4, so a stage of n workgroups on 256 compute units takes
+// about (zc + 4) max(alone, ceil(n / 256) busy), rounded off where the two meet (their fourth powers are
+// added).  Rows: FP32, FP64; per row stages without AT stencils, with AT on tiles aligned with the PEs,
+// with masked AT.  Tiles that won nowhere are left out.
+//
+// The pairs are estimates from stage times on ten grids of 32^3 to 270 x 200 x 150 (32 x 8 tiles without
+// AT, FP32, 32^3: 18.3 us with z chunks of 4, 43 with 16).  Against every shape timed there (2,500 stage
+// times) the model's median is between 0.83 and 1.19 of the time for all pairs but two: masked FP32
+// stages with 16 x 8 tiles are priced 1.43 times too dear (busy 1.5 would fit), aligned FP64 ones with
+// 32 x 4 tiles 1.7 times.  In FP64 with AT, 16 x 16 tiles (6) were given the pair of the 32 x 8 ones (1),
+// and time like them (1.06 and 1.14 against 1.13 and 1.17).  The shape that comes out is within 5% of
+// the fastest in 34 of the 40 cases; the worst are 200^3 FP32 without AT (300 us with 32 x 8 tiles and
+// chunks of 50, 254 with 64 x 8 and 40) and 100^3 FP32 with masked AT (102 with 16 x 16 and 10, 88 with
+// 16 x 8 and 14).
 struct ShapeCost {
   int tile;
   double alone, busy;
@@ -135,7 +142,7 @@ double march_cost(const ShapeCost& c, int64_t workgroups, int zc) {
 void default_shape(const Geom& g, int precision, bool forced, bool at, int* tile, int* zchunk) {
   const int row = precision == AT_FP32 ? 0 : 1;
   double least = 1e300;
-  for (int i = 0; i < kShapes; ++i) {
+  for (int i = 0; i < kShapes; ++i) {  // in the row's order: a tile replaces the choice so far if it saves 5% on it
     const int t = kShapeCost[row][at ? 1 : 0][i].tile;
     if (fused_lds_bytes(t, row == 0 ? 4 : 8, forced) > kLdsBytes) continue;
     const ShapeCost* c = kShapeCost[row][!at ? 0 : tile_aligned(g, t) ? 1 : 2];

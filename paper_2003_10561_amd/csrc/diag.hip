@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kPtsBX* kPtsBY) void k_diag_pts(const T* __restrict
   }
 }
 
-constexpr int kHistPts = 8, kHistWGs = 2048;  // points per thread and step; workgroups at most  // points per thread of the histogram pass
+constexpr int kHistPts = 8, kHistWGs = 2048;  // points per thread and step; workgroups at most
 
 // Counts of eps / <eps> and Omega / <Omega> (means from the reduced sums) in LDS, flushed with
 // 64-bit integer atomics.  The flushes of all workgroups meet on the same few addresses: at most
@@ -750,7 +750,6 @@ int plan_of(const at_config* cfg, const at_diag_params* prm, Plan* pl) {
   const int64_t tiles = (int64_t)((p.nx + kPtsBX - 1) / kPtsBX) * ((p.ny + kPtsBY - 1) / kPtsBY);
   p.pts_zc = (int)std::min<int64_t>(kPtsZC, std::max<int64_t>(4, tiles * p.nz / 512));
   p.pts_grid = dim3((p.nx + kPtsBX - 1) / kPtsBX, (p.ny + kPtsBY - 1) / kPtsBY, (p.nz + p.pts_zc - 1) / p.pts_zc);
-  const int64_t nblk64 = (int64_t)((p.nx + 63) / 64) * ((p.ny + 3) / 4) * ((p.nz + 31) / 32);
   p.nwgz = (int64_t)4 * p.ny * p.nbxz;
   p.spanmax = p.nz / 2 + p.bxz + 2;  // |k| grows by at most bx - 1 + nz/2 across one workgroup
   size_t o = 0;
@@ -762,7 +761,6 @@ int plan_of(const at_config* cfg, const at_diag_params* prm, Plan* pl) {
   p.off_S = take((size_t)4 * p.nz * p.ny * p.px * sizeof(double2));
   p.off_eo = take((size_t)p.nx * p.ny * p.nz * sizeof(double2));
   p.off_tw = take((size_t)p.ntw * sizeof(double2));
-  take((size_t)nblk64 * kMom * sizeof(double));  // (spare: the size that callers have allotted stays)
   p.off_mid = take((size_t)kRed * kMom * sizeof(double));
   p.off_sums = take(8 * sizeof(double));
   p.off_hist = take((size_t)2 * (prm->nbins + 1) * sizeof(unsigned long long));

@@ -345,6 +345,8 @@ int64_t update_blocks(const Geom& g) {
   const dim3 gr = grid_of(g);
   return (int64_t)gr.x * gr.y * gr.z;
 }
+// Room for the statistics partials, counted in blocks of 64 x 4 points of one plane: a measure of the grid
+// that stays when the march is cut otherwise (k_stats leaves fewer partials, one per stats_workgroups).
 int64_t stats_blocks(const Geom& g) { return update_blocks(g); }
 
 const char* kernel_name(int id) {

@@ -14,7 +14,8 @@
 
 using namespace atns;
 
-// Largest number of statistics blocks (64 x 4 points of one z plane each): 256^3 needs 65536.
+// Largest grid, counted in blocks of 64 x 4 points of one z plane: 256^3 has 65536.  (The kernels leave
+// a partial per 64 x 8 columns of several planes, so the scratch holds more than they need.)
 constexpr int64_t kNoallocMaxBlocks = 65536;
 constexpr size_t kScratchDoubles = (size_t)kNoallocMaxBlocks * kNStat + kStatOutBytes / sizeof(double);
 static_assert(AT_STATS_NOALLOC_MAX_BLOCKS == kNoallocMaxBlocks, "header and library limits agree");
@@ -66,8 +67,8 @@ int at_field_stats_noalloc(const at_config* cfg, const void* dev_q, at_stats_t* 
   if (!dev_q || !dev_out) return fail(AT_E_INVAL, "NULL field or output pointer");
   const Geom g = make_geom(cfg);
   if (stats_blocks(g) > kNoallocMaxBlocks)
-    return fail(AT_E_INVAL, "grid needs more statistics blocks (ceil(nx/64) ceil(ny/4) nz) than the "
-                            "allocation-free scratch holds (65536)");
+    return fail(AT_E_INVAL, "grid larger than the allocation-free statistics take: more than 65536 blocks of "
+                            "64 x 4 points of a plane (ceil(nx/64) ceil(ny/4) nz)");
   double* sc = nullptr;
   rc = scratch_of_device(&sc);
   if (rc) return rc;

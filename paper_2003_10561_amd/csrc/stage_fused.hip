@@ -695,18 +695,18 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
       // allocation, 1% of its SUB stages)
       if (kBlock && wx) {
         if (kSub && kcx > 0) {
-        // a halo column next to its own delayed x face: its AT sums, formed a plane ahead, or from
-        // the two extrapolated values at its face's reader slots
-        if (kHv) {
+          // a halo column next to its own delayed x face: its AT sums, formed a plane ahead, or from
+          // the two extrapolated values at its face's reader slots
+          if (kHv) {
 #pragma unroll
-          for (int c = 0; c < 4; ++c) sx[c] = s_hv[c][hslot];
-        } else {
-          const uint32_t o = (uint32_t)gz * zsx + opx - (uint32_t)(lxe < 2 ? lxe : lxe - a.ex + 2);
-          const bool lo = lxe < 2, outer = lxe == 0 || lxe == a.ex - 1;
+            for (int c = 0; c < 4; ++c) sx[c] = s_hv[c][hslot];
+          } else {
+            const uint32_t o = (uint32_t)gz * zsx + opx - (uint32_t)(lxe < 2 ? lxe : lxe - a.ex + 2);
+            const bool lo = lxe < 2, outer = lxe == 0 || lxe == a.ex - 1;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) sx[c] = at_sum_of<T>(lo, outer, a.gv[o + (uint32_t)c * a.slab0],
-                                                            a.gv[o + 1 + (uint32_t)c * a.slab0]);
-        }
+            for (int c = 0; c < 4; ++c) sx[c] = at_sum_of<T>(lo, outer, a.gv[o + (uint32_t)c * a.slab0],
+                                                              a.gv[o + 1 + (uint32_t)c * a.slab0]);
+          }
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(sx[c]));  // (keeps the block a block)
@@ -719,11 +719,11 @@ __device__ __forceinline__ void stage_body(const FArgs<T>& a, const int mode, co
       }
       if (kBlock && wy) {
         if (kSub && kcy > 0) {
-        const uint32_t o = (uint32_t)gz * zsy + opy - (uint32_t)(lye < 2 ? lye : lye - a.ey + 2) * (uint32_t)nx;
-        const bool lo = lye < 2, outer = lye == 0 || lye == a.ey - 1;
+          const uint32_t o = (uint32_t)gz * zsy + opy - (uint32_t)(lye < 2 ? lye : lye - a.ey + 2) * (uint32_t)nx;
+          const bool lo = lye < 2, outer = lye == 0 || lye == a.ey - 1;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sy[c] = at_sum_of<T>(lo, outer, a.gv[o + (uint32_t)c * a.slab1],
-                                                          a.gv[o + (uint32_t)nx + (uint32_t)c * a.slab1]);
+          for (int c = 0; c < 4; ++c) sy[c] = at_sum_of<T>(lo, outer, a.gv[o + (uint32_t)c * a.slab1],
+                                                            a.gv[o + (uint32_t)nx + (uint32_t)c * a.slab1]);
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(sy[c]));

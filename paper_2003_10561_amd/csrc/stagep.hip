@@ -502,7 +502,7 @@ __global__ __launch_bounds__(256) void kp_rhs(PA<T> a) {
   block_totals(a, tsum, b.L, threadIdx.y * kBXp + threadIdx.x);
 }
 
-// Tiled kernels, for PEs whose x and y edges fill tiles of up to kTB x kTB columns well (paper_tile): a
+// Tiled kernels, for PEs whose x and y edges fill tiles of up to kTB x kTB columns well (paper_plan): a
 // workgroup owns a column tile inside one PE and marches it through tz planes.  A PE's face is cut into
 // equal tiles, the last of a row or column maybe narrower; threads outside a narrower tile only help
 // with its halo.  Per plane, the tile's points and their 2-wide x and y halos are written once to LDS
@@ -1016,7 +1016,12 @@ PaperPlan paper_plan(const Geom& g) {
   p.zcm = (int)std::max<int64_t>(8, std::min<int64_t>(64, cols * g.n[2] / 2048));
   p.brick_blocks = cols * cdiv(g.n[2], p.zc);
   p.mixed_blocks = cols * cdiv(g.n[2], p.zcm);
-  // tiles: a PE's edge in equal parts of at most kTB; worth it where the tile fills half its threads
+  // tiles: a PE's edge in equal parts of at most kTB, taken where the tile fills half its threads.  Points
+  // against tiles, us a step on grids of about 96^3: PEs of 16 x 16 407 and 297 (FP64 744 and 572), 12 x 12
+  // 426 and 327 (774 and 761), 16 x 8 412 and 394 (785 and 886), 10 x 10 452 and 528 (897 and 1223).  So
+  // the line is where a tile that covers its PE breaks even in FP32; in FP64 that is at about 150 points.
+  // It lies low for PEs of several tiles, 17 x 15 (9 + 8 by 15) 392 and 447 (725 and 889), and for grids
+  // that leave compute units idle, 48^3 on PEs of 24 x 16 x 6 121 and 244 (187 and 315).
   for (int d = 0; d < 2; ++d) {
     p.tn[d] = cdiv(g.e[d], kTB);
     p.tw[d] = cdiv(g.e[d], p.tn[d]);

@@ -77,8 +77,9 @@ def test_paper_rhs_random_delays_history_levels(visc, n, p, seed):
     """RHS with six supplied levels and random delays 0..3 on every face at the current step: every
     ghost level, both viscosity laws.  A ragged grid (40 x 20 x 10 on 4 x 2 x 2 PEs of 10 x 10 x 5)
     runs the point-per-thread kernels; PEs of 16 x 16 x 10 run the LDS tiles, whose halos then
-    hold the extrapolated values of delayed x and y faces; at 80 planes the tiles' second z chunk
-    (64 planes each) starts inside a PE, with six z-PEs in the first."""
+    hold the extrapolated values of delayed x and y faces; grids this small are marched 8 planes at a
+    time, so most chunks start inside a z-PE of 10 and touch one or two (longer marches over more
+    z-PEs: test_gpu_tiles.py)."""
     nlev = 6
     say(f"case paper-form rhs {n} on {p}, visc {visc}")
     dt = 2e-3

@@ -69,17 +69,18 @@ def check(n, p, order=4, form=0, steps=2, precision="fp64", tol=TOL64, tune=None
     g.close()
 
 
-# edges: 6 (the smallest PE: 36 columns, two halo points a thread), 7 (one partial tile in z), 21 and
-# 25 (odd), 33 (tiles of 17 + 16), 65 (of 33 + 32), 40 along z (cut into chunks of 8)
+# edges: 6 (the smallest PE: 36 columns, two halo points a thread), 7 (two halo points a thread), 40 along z
+# (cut into chunks of 8), 21 x 25 (rows of 9 + 9 + 7; z chunks of 9 + 9 + 9 + 6), 33 x 21 (one column of
+# tiles 33 wide, rows of 7), 65 (columns of 22 + 22 + 21)
 @pytest.mark.parametrize("n,p", [((6, 6, 6), (1, 1, 1)), ((12, 14, 40), (2, 2, 1)), ((42, 25, 33), (2, 1, 1)),
                                  ((33, 21, 24), (1, 1, 3)), ((130, 9, 12), (2, 1, 1))])
 def test_order6_tiles(n, p):
     check(n, p, order=6)
 
 
-# the paper's form: edges 5 (the smallest PE), 9 and 11 (tiles of 9 x 11 use 99 of 256 threads: a point
-# per thread), 12 and 11 (132: a partial tile), 17 (9 + 8) and 33 (three tiles, z cut into chunks that
-# start inside a PE), grids of fewer columns than a brick
+# the paper's form: edges 5 (the smallest PE), 9 x 11 (99 of 256 threads: a point per thread), 12 x 11
+# (132: a partial tile), 17 x 33 (9 + 8 by 11 + 11 + 11: 99 again, a point per thread), 33 x 16 (three
+# equal tiles, chunks of 8 planes that start inside z-PEs of 20), grids of fewer columns than a brick
 @pytest.mark.parametrize("n,p", [((10, 5, 15), (2, 1, 3)), ((18, 22, 10), (2, 2, 1)), ((12, 22, 30), (1, 2, 2)),
                                  ((34, 33, 18), (2, 1, 3)), ((66, 16, 40), (2, 1, 2))])
 def test_paper_form_tiles(n, p):
