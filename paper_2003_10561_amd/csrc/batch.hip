@@ -14,10 +14,10 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <iterator>
 #include <new>
 #include <sstream>
 #include <string>
-#include <utility>
 #include <vector>
 
 #include "sim_internal.h"
@@ -529,41 +529,37 @@ int do_autotune(at_batch* b, const char* cache, int reps, double* best_ms) {
   }
   int maxz = 4;
   for (const at_sim* s : b->runs) maxz = std::max(maxz, s->cfg.n[2]);
-  // The candidates: every tile with the z chunks of kZ, then the shapes in force and, of a lone member,
-  // those it has by itself.  Its default is often a chunk that kZ lacks (32^3 in FP64: chunks of 4
-  // planes, 104 us a step; the best of kZ, 8 planes, 148 us), and tuning must not lose to it.
-  static const int kZ[] = {8, 16, 32, 64, 128, 256, 512};
-  std::vector<std::pair<int, int>> shapes;
-  auto offer = [&](int tile, int zc) {
-    const std::pair<int, int> sh(tile, zc);
-    if (tile_fits(b, tile) && std::find(shapes.begin(), shapes.end(), sh) == shapes.end()) shapes.push_back(sh);
-  };
-  for (int tile = 0; tile < kTileCount; ++tile)
-    for (int zc : kZ)
-      if (zc <= maxz || zc == kZ[0]) offer(tile, zc);
-  offer(b->tile, std::min(b->zchunk, maxz));
-  offer(b->tile_d, std::min(b->zchunk_d, maxz));
-  if (b->runs.size() == 1) {
-    offer(b->runs[0]->tile, b->runs[0]->zchunk);
-    offer(b->runs[0]->tile_d, b->runs[0]->zchunk_d);
-  }
   double best_s = 1e300, best_d = 1e300;
   int bt = b->tile, bz = b->zchunk, btd = b->tile_d, bzd = b->zchunk_d;
-  for (const auto& [tile, zc] : shapes) {
-    double m_sync = 0.0, m_at = 0.0;
-    int rc = trial_stage<T>(b, tile, zc, reps, false, &m_sync);
-    if (!rc && f > 0.0) rc = trial_stage<T>(b, tile, zc, reps, true, &m_at);
+  auto offer = [&](bool delayed, int tile, int zc) -> int {
+    double m = 0.0;
+    const int rc = trial_stage<T>(b, tile, zc, reps, delayed, &m);
     if (rc) return rc;
-    if (m_sync < best_s) {
-      best_s = m_sync;
-      bt = tile;
-      bz = zc;
+    if (m < (delayed ? best_d : best_s)) {
+      (delayed ? best_d : best_s) = m;
+      (delayed ? btd : bt) = tile;
+      (delayed ? bzd : bz) = zc;
     }
-    if (f > 0.0 && m_at < best_d) {
-      best_d = m_at;
-      btd = tile;
-      bzd = zc;
+    return AT_OK;
+  };
+  static const int kZ[] = {8, 16, 32, 64, 128, 256, 512};
+  for (int tile = 0; tile < kTileCount; ++tile) {
+    if (!tile_fits(b, tile)) continue;
+    for (int zc : kZ) {
+      if (zc > maxz && zc != kZ[0]) break;
+      int rc = offer(false, tile, zc);
+      if (!rc && f > 0.0) rc = offer(true, tile, zc);
+      if (rc) return rc;
     }
+  }
+  // A lone member's own shapes compete too: its default is often a z chunk that kZ lacks (32^3 in FP64:
+  // chunks of 4 planes, 103 us a step; the best of kZ, 8 planes, 148 us), and tuning must not lose to it.
+  if (b->runs.size() == 1) {
+    const at_sim* s = b->runs[0];
+    auto in_kz = [&](int zc) { return std::find(std::begin(kZ), std::end(kZ), zc) != std::end(kZ); };
+    int rc = in_kz(s->zchunk) ? AT_OK : offer(false, s->tile, s->zchunk);
+    if (!rc && f > 0.0 && !in_kz(s->zchunk_d)) rc = offer(true, s->tile_d, s->zchunk_d);
+    if (rc) return rc;
   }
   if (!(f > 0.0)) {  // no delayed stage ahead: both kinds in the synchronous choice
     btd = bt;
