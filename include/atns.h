@@ -204,7 +204,8 @@ ATNS_API int at_field_device(at_sim* sim, void** dev_ptr);
  * tile and register budget (0: 64x8, 1: 32x8, 2: 32x8 at higher occupancy, 3: 32x4, 4: 64x4,
  * 5: 16x8, 6: 16x16 points in x-y), `zchunk` (>= 4) the number of z planes each workgroup marches through.
  * Results do not depend on either (every point is computed by the same arithmetic); only speed
- * does.  Set by the autotuner.  at_set_tuning sets the shape of every stage, at_get_tuning returns
+ * does.  A new run takes the shapes of least cost in a model of the march; the autotuner picks them
+ * from timed trials.  at_set_tuning sets the shape of every stage, at_get_tuning returns
  * that of the stages that read no delayed level.  Errors: AT_E_INVAL. */
 #define AT_N_TILES 7
 ATNS_API int at_set_tuning(at_sim* sim, int32_t tile, int32_t zchunk);
@@ -249,8 +250,8 @@ ATNS_API int at_destroy(at_sim* sim);
  *   hip_stream: the stream (NULL = default) on the current device; the call only enqueues.
  * The per-block partials and the reduction live in a static device array of the library, one per
  * device, sized for AT_STATS_NOALLOC_MAX_BLOCKS blocks of 64 x 4 points of one z plane
- * (ceil(nx / 64) ceil(ny / 4) nz <= 65536, e.g. up to 256^3; about 6.9 MB), held until the process
- * ends.  Every call on a device shares that array and leaves its contents there: calls that overlap
+ * (ceil(nx / 64) ceil(ny / 4) nz <= 65536, e.g. up to 256^3; about 6.9 MB; the kernels leave fewer
+ * partials), held until the process ends.  Every call on a device shares that array and leaves its contents there: calls that overlap
  * on one device (other streams or host threads without ordering between them) race.
  * Errors: AT_E_INVAL (NULL pointers, bad config, a grid beyond the block limit), AT_E_HIP. */
 #define AT_STATS_NOALLOC_MAX_BLOCKS 65536

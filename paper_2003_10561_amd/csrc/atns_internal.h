@@ -141,14 +141,14 @@ hipError_t launch_at_sums_batch(const void* runs, const uint2* work, int64_t nbl
 int64_t view_blocks(const Geom& g);  // 256-point blocks of k_at_sums for one run
 constexpr int kModeStepH = 0, kModeRhsH = 1, kModePublishH = 2;
 
-// Kernel identities for timing (names in kernel_name()).
+// Kernel identities for timing (names in kernel_name(); the paper form's kp_mixed counts as kp_rhs).
 enum KernelId {
   kKStage = 0, kKRhs = 1, kKPublish = 2, kKForce = 3, kKStats = 4, kKGhost = 5, kK6Grad = 6, kK6Div = 7,
   kKPPublish = 8, kKPGrad = 9, kKPRhs = 10, kK6Ghost = 11, kKCount = 12
 };
 
-// The paper's own discretisation (stagep.hip, form 1): publication of the conserved variables,
-// then per stage the AT gradients and the right-hand side with the update, one point per thread.
+// The paper's own discretisation (stagep.hip, form 1): per stage the AT gradients (publishing the conserved
+// variables at stage 1), the mixed derivatives, and the right-hand side with the update.
 template <typename T>
 struct StagePArgs {
   Geom g;
