@@ -107,7 +107,7 @@ Geom make_geom(const at_config* c) {
 // added).  Rows: FP32, FP64; per row stages without AT stencils, with AT on tiles aligned with the PEs,
 // with masked AT.  Tiles that won nowhere are left out.
 //
-// The pairs are estimates from stage times on ten grids of 32^3 to 270 x 200 x 150 (32 x 8 tiles without
+// The pairs are estimates from stage times on ten grids of 32^3 to 256^3 (32 x 8 tiles without
 // AT, FP32, 32^3: 18.3 us with z chunks of 4, 43 with 16).  Against every shape timed there (2,500 stage
 // times) the model's median is between 0.83 and 1.19 of the time for all pairs but two: masked FP32
 // stages with 16 x 8 tiles are priced 1.43 times too dear (busy 1.5 would fit), aligned FP64 ones with
